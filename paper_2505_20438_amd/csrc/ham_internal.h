@@ -193,6 +193,8 @@ constexpr int PART_ROWS = 1024;
 // returns GEMM_NO_STAGE (nothing launched) when a staged X source does not fit
 int launch_gemm(int dtype, int epi, const GemmArgs& a, int max_split, Stream s, int tag, int* nsplit);
 constexpr int GEMM_NO_STAGE = -2;
+// bf16 GEMMs of more rows than a decode batch has (kernels_prompt.hip; launch_gemm takes it by itself)
+int launch_gemm_prompt(int epi, const GemmArgs& a, int max_split, Stream s, int* nsplit);
 // whether launch_gemm would take the staged path for these arguments (nothing launched)
 bool gemm_stage_fits(int dtype, int epi, const GemmArgs& a, int max_split);
 // the NormOut epilogue (one workgroup per 16-column tile, unsplit): rows up to

@@ -20,8 +20,9 @@
 //    would produce X disappears from the launch sequence.
 //  * k_gemm_wide (8 < M <= 256: batched decode, micro context rows): eight
 //    waves own eight column tiles and share X chunks through LDS.
-//  * k_gemm_big (larger M: prefill chunks): 128x128 LDS-staged tiles, double
-//    buffered, 2x2 waves of 64x64.
+//  * larger M (prompt chunks): kernels_prompt.hip in bf16; in fp32 k_gemm_pf
+//    (M > 256, LDS ring) and k_gemm_big (128x128 LDS-staged tiles, double
+//    buffered, 2x2 waves of 64x64).
 // X rows are the A operand (padded to 16), weight rows the B operand, so the
 // accumulator's columns are output features: lane l holds column l & 15 of a
 // 16-column tile for rows 4*(l >> 4) + i.
@@ -30,36 +31,10 @@
 
 #include "decide.h"
 #include "device_common.h"
+#include "gemm_epilogue.h"
 #include "ham_internal.h"
 
 namespace ham {
-
-// Epilogue of one accumulator element: row m, column nb + r16 of the tile at nb.
-// Every lane must call it (the SwiGLU pairing exchanges values between lanes).
-template <typename T, int EPI>
-__device__ __forceinline__ void epi_tile(const GemmArgs& a, int m, bool ok, int nb, int r16, float v) {
-  const int n = nb + r16;
-  if constexpr (EPI == EPI_SWIGLU) {
-    // a 16-row tile holds gate rows of 8 features then their up rows
-    const float u = __shfl_xor(v, 8, WAVE);
-    if (ok && r16 < 8) {
-      const float sg = v / (1.0f + expf(-v));
-      Act<T>::put(a.out, m, a.ldo, nb / 2 + r16, sg * u);
-    }
-  } else {
-    if (!ok) return;
-    if constexpr (EPI == EPI_F32) {
-      ((float*)a.out)[(size_t)m * a.ldo + n] = v;
-    } else if constexpr (EPI == EPI_OP) {
-      Act<T>::put(a.out, m, a.ldo, n, v);
-    } else if constexpr (EPI == EPI_RESID) {
-      float* o = (float*)a.out + (size_t)m * a.ldo;
-      o[n] += v;
-    } else if constexpr (EPI == EPI_XMASK) {
-      if (a.rowmask[m]) ((float*)a.out)[(size_t)m * a.ldo + n] = v;
-    }
-  }
-}
 
 __device__ __forceinline__ bool better(float v, int i, float bv, int bi) {
   return v > bv || (v == bv && i < bi);
@@ -1147,8 +1122,8 @@ __global__ __launch_bounds__(256) void k_gemm_big(GemmArgs a) {
     }
 }
 
-// ------------------------------------------------------------------------ prompt GEMM
-// Prompt chunks (M > 256 rows): a BM x 128 output tile per workgroup of BM/32
+// ------------------------------------------------------------------------ prompt GEMM, fp32
+// Prompt chunks (M > 256 rows) of fp32 models: a BM x 128 output tile per workgroup of BM/32
 // waves (64 x 64 each), k in steps of one fragment (KB).  Every operand
 // fragment a wave reads is one 1 KB block in lane order, and it lands in LDS
 // in that order straight from memory (global_load_lds_dwordx4: no registers
@@ -1162,13 +1137,6 @@ __global__ __launch_bounds__(256) void k_gemm_big(GemmArgs a) {
 #define HAM_PF_NS 3
 #endif
 constexpr int PF_NS = HAM_PF_NS;
-
-// s_waitcnt with vmcnt <= n (0..63) and lgkmcnt = 0 (expcnt untouched)
-template <int N>
-__device__ __forceinline__ void wait_vm_lgkm0() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
-}
 
 // Output tile of a prompt-GEMM workgroup.  Workgroups go to the 8 XCDs in
 // turn (linear id mod 8), and each XCD has its own L2: the grid is renumbered
@@ -1488,14 +1456,13 @@ static int gemm_t(const GemmArgs& a0, int max_split, int tag, Stream s, int* nsp
     if constexpr (EPI == EPI_ARGMAX) {
       return -1;
     } else {
-#ifndef HAM_PF_BN
-#define HAM_PF_BN 256
-#endif
-      if (a.M > 256) {
+      if constexpr (std::is_same<T, bf16>::value) {
+        return launch_gemm_prompt(EPI, a, max_split, s, nsplit_out);
+      } else if (a.M > 256) {
         constexpr int BM = 128;
         // 256-column tiles (64 x 128 per wave: half the operand reads from LDS per
         // product of 64 x 64) while they still give at least two workgroups per CU
-        if (HAM_PF_BN == 256 && (long)((a.N + 255) / 256) * ((a.M + BM - 1) / BM) >= 512) {
+        if ((long)((a.N + 255) / 256) * ((a.M + BM - 1) / BM) >= 512) {
           dim3 grid((a.N + 255) / 256, (a.M + BM - 1) / BM);
           launch_k((k_gemm_pf<T, EPI, BM, 256>), grid, dim3(BM / 64 * 2 * 64), 0, s, a);
         } else {
@@ -1503,10 +1470,11 @@ static int gemm_t(const GemmArgs& a0, int max_split, int tag, Stream s, int* nsp
           launch_k((k_gemm_pf<T, EPI, BM, 128>), grid, dim3(BM / 64 * 2 * 64), 0, s, a);
         }
         return 0;
+      } else {
+        dim3 grid((a.N + 127) / 128, (a.M + 127) / 128);
+        launch_k((k_gemm_big<T, EPI>), grid, dim3(256), 0, s, a);
+        return 0;
       }
-      dim3 grid((a.N + 127) / 128, (a.M + 127) / 128);
-      launch_k((k_gemm_big<T, EPI>), grid, dim3(256), 0, s, a);
-      return 0;
     }
   }
   const int nfr = a.K / KB;
