@@ -275,6 +275,11 @@ struct ham_model {
   // typed views
   template <typename P> P* W(size_t off) const { return (P*)(w + off); }
   template <typename P> P* WS(size_t off) const { return (P*)(ws + off); }
+  // split-K partials of a GEMM go to the workspace's partial buffer
+  void set_part(GemmArgs& g) const {
+    g.part = WS<float>(y.part);
+    g.part_cap = (long)PART_ROWS * y.Nmax;
+  }
 };
 
 namespace {
@@ -337,6 +342,19 @@ int norm_rows(ham_model* m, float* x, int R, int stride, int off, const float* g
   return rc ? fail(HAM_EINVAL, "rmsnorm shape") : HAM_OK;
 }
 
+// Adds a pending split-K result to the rows of x (where no norm follows that would).
+int fold_pending(ham_model* m, float* x, int R, Pending& pend) {
+  const Layout& y = m->y;
+  if (pend.part) {
+    NormArgs na{};
+    na.x = x; na.ldx = y.d; na.row_stride = 1; na.d = y.d; na.R = R;
+    na.part = pend.part; na.nsplit = pend.nsplit; na.pM = pend.M; na.ss = m->WS<float>(y.nss);
+    if (launch_fold(na, m->s)) return fail(HAM_EINVAL, "partials shape");
+  }
+  pend = Pending{};
+  return HAM_OK;
+}
+
 // The RMSNorm feeding GEMM `ga` (rows x, gain g): where the batched GEMM can
 // build the normed operand itself (XS_NORMW), only the norm's first phase
 // launches; otherwise the whole norm writes the operand buffer (XS_ACT).
@@ -374,7 +392,7 @@ int layer_tail(ham_model* m, int j, int R, float* x, int split, const int* gate,
   const Layout& y = m->y;
   int ns = 1;
   GemmArgs ga{};
-  ga.part = m->WS<float>(y.part); ga.gate = gate; ga.gate_n = gate_n; ga.M = R;
+  m->set_part(ga); ga.gate = gate; ga.gate_n = gate_n; ga.M = R;
   ga.W = m->W<char>(y.Wo[j]); ga.N = y.d; ga.K = y.HD; ga.X = m->WS<char>(y.ao); ga.ldx = y.HD;
   ga.out = x; ga.ldo = y.d;
   if (gemm_p(m, EPI_RESID, ga, split, gk(HAM_PROF_O), &ns)) return fail(HAM_EINVAL, "o-proj gemm shape");
@@ -613,10 +631,12 @@ int run_layer(ham_model* m, int j, int R, const RowMap& rm, float*& x, bool pref
   if (step)
     return run_layer_step(m, j, R, rm, x, Kc, VTc, sb, sh, S, attn_split, gate, gate_n, pend, ctx_prev, ldctx,
                           kv_visible, *step, base, g_next, ctx_out);
-  const int split = prefill ? 1 : MAX_GEMM_SPLIT;
+  // a prompt's GEMMs split too (512 rows of the 1B shape: o-projection and down 64 workgroups unsplit, 38 and 131 us
+  // against 18 and 40); not in fp32, where the tiny model's prompt gained 0.4% by it
+  const int split = prefill && dt == HAM_F32 ? 1 : MAX_GEMM_SPLIT;
   int ns = 1;
   GemmArgs ga{};
-  ga.part = m->WS<float>(y.part); ga.gate = gate; ga.gate_n = gate_n;
+  m->set_part(ga); ga.gate = gate; ga.gate_n = gate_n;
   ga.W = m->W<char>(y.Wqkv[j]); ga.N = y.QKV; ga.K = y.d; ga.M = R;
   ga.out = m->WS<float>(y.qkv); ga.ldo = y.QKV;
   if (prefill) {
@@ -676,7 +696,9 @@ int run_layer(ham_model* m, int j, int R, const RowMap& rm, float*& x, bool pref
     aa.rm = r1;
     aa.nsplit = attn_splits_for(dt, 1, y.Hk, r1.t0 + 1);
     if (launch_attn_decode(dt, aa, s) != 0) return fail(HAM_EINVAL, "attention shape");
-    return layer_tail(m, j, 1, x + (size_t)(R - 1) * y.d, split, gate, gate_n, pend, gk);
+    float* xl = x + (size_t)(R - 1) * y.d;
+    if (int rc = layer_tail(m, j, 1, xl, split, gate, gate_n, pend, gk)) return rc;
+    return fold_pending(m, xl, 1, pend);
   }
   m->pbegin(base ? HAM_PROF_ATTN : -1, (double)kv_visible * y.Hk * y.hd * 2 * y.es);
   const int arc = prefill ? launch_attn_prefill(dt, aa, s) : launch_attn_decode(dt, aa, s);
@@ -956,17 +978,21 @@ int prefill_common(ham_model* m, int32_t batch, int32_t T, const int32_t* d_prom
       launch_gather_rows(dt, g, s);
       RowMap rm{};
       rm.mode = ROWS_PREFILL; rm.b = b; rm.t0 = t0; rm.pos = d_positions; rm.ldpos = T; rm.st = m->sp;
+      Pending pend;  // a layer's split down projection, folded in by the next layer's norm
       for (int l = 0; l < y.L; ++l) {
-        Pending none;
         // the last layer's outputs are read only at the prompt's last row (the
         // decision and the context rows): earlier chunks append its K and V
         // only, the last chunk runs attention and tail on that row alone
         const bool kv_only = !last && l == y.L - 1;
         const bool last_row = last && l == y.L - 1 && R > 1;
         int rc = run_layer(m, l, R, rm, xp, true, m->st + y.Kc + l * y.kv_layer, m->st + y.VTc + l * y.kv_layer,
-                           sb, sh, y.S, 1, nullptr, 0, none, nullptr, 0, 0, nullptr, nullptr, nullptr, false, kv_only,
+                           sb, sh, y.S, 1, nullptr, 0, pend, nullptr, 0, 0, nullptr, nullptr, nullptr, false, kv_only,
                            last_row);
         if (rc) return rc;
+        bool read_here = last && l == y.L - 1;  // the output rows are read before another norm
+        if (last)
+          for (int c = 0; c < y.C; ++c) read_here |= y.ctx_l[c] == l + 1;
+        if (read_here && (rc = fold_pending(m, xp, R, pend))) return rc;
         if (last)
           for (int c = 0; c < y.C; ++c)
             if (y.ctx_l[c] == l + 1)
@@ -1028,7 +1054,7 @@ int macro_step_body(ham_model* m, int32_t* d_out_tokens, int32_t* d_out_lens) {
   float* x = m->WS<float>(y.x);
   // compositional embedder (Sec. 3.2), skipped on device unless some group has > 1 token
   GemmArgs ga{};
-  ga.part = m->WS<float>(y.part); ga.gate = m->sp.fused; ga.gate_n = B;
+  m->set_part(ga); ga.gate = m->sp.fused; ga.gate_n = B;
   ga.W = m->W<char>(y.Aqkv); ga.N = 3 * y.HD; ga.K = y.d; ga.X = m->WS<char>(y.emb_in); ga.ldx = y.d;
   ga.M = 5 * B; ga.out = m->WS<float>(y.qkv); ga.ldo = 3 * y.HD;
   int ns = 1;

@@ -105,7 +105,7 @@ struct DecideArgs {
 //    (never x itself: other workgroups are still reading it) and to ctx.
 //  XS_ATTN: X = attention output combined from the split records of the
 //    decode attention (log-sum-exp weights per head, splits in order).
-//  XS_NORMW (batched GEMM, 8 < M <= 256): X = g * x * rinv from fp32 rows x whose
+//  XS_NORMW (batched GEMM, 8 < M <= 64, in fp32 256): X = g * x * rinv from fp32 rows x whose
 //    pending partials the norm's first phase has already folded in; rinv from
 //    that phase's 256-column chunk sums of squares ssw [M][nchw].
 enum XSource { XS_ACT = 0, XS_NORM = 1, XS_ATTN = 2, XS_NORMW = 3 };
@@ -147,6 +147,7 @@ struct GemmArgs {
   const int* rowmask;              // XMASK: rows to store
   const int* gate; int gate_n;     // launch does nothing unless a gate flag is set
   float* part; int* counters; int nsplit;  // split-K partials [nsplit][M][N] (written when nsplit > 1)
+  long part_cap;                   // floats in part that a prompt GEMM may fill (0: it does not split)
   DecideArgs dec;                  // ARGMAX only
   int xsrc; XStage xs;             // X operand source (XS_ACT: X above)
   NormOut no;                      // RESID only
@@ -236,6 +237,8 @@ struct NormArgs {
   float* ss;                                          // scratch [R][d/256] for the two-phase form, or null
 };
 int launch_rmsnorm(int dtype, const NormArgs& a, Stream s);
+// the partials alone added to the rows (a.ss: scratch as above)
+int launch_fold(const NormArgs& a, Stream s);
 // the norm's first phase alone, for 16..256 rows feeding an XS_NORMW GEMM (-1: does not apply)
 int launch_norm_reduce(const NormArgs& a, Stream s);
 

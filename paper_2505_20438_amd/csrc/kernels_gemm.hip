@@ -18,7 +18,7 @@
 //    is built in LDS by a prologue (an RMSNorm of the residual plus pending
 //    partials, or the merge of the attention splits), so the kernel that
 //    would produce X disappears from the launch sequence.
-//  * k_gemm_wide (8 < M <= 256: batched decode, micro context rows): eight
+//  * k_gemm_wide (8 < M <= 64, in fp32 256: batched decode, micro context rows): eight
 //    waves own eight column tiles and share X chunks through LDS.
 //  * larger M (prompt chunks): kernels_prompt.hip in bf16; in fp32 k_gemm_pf
 //    (M > 256, LDS ring) and k_gemm_big (128x128 LDS-staged tiles, double
@@ -726,13 +726,19 @@ __global__ __launch_bounds__(STG_THREADS) void k_gemm_staged(GemmArgs a) {
 }
 
 // ------------------------------------------------------------------------ wide
-// Batched skinny GEMM (8 < M <= 256 rows): a workgroup of eight waves owns eight
+// Batched skinny GEMM (8 < M <= WIDE_MAX_M rows): a workgroup of eight waves owns eight
 // column tiles of 16*TN columns (one per wave) and one k-range.  The X rows of
 // the k-range pass through LDS in chunks of WIDE_KC columns shared by the eight
 // waves, so a workgroup reads X once for eight tiles instead of once per tile;
 // each wave streams its own weight blocks with the next chunk in flight.  Waves
 // own disjoint columns, so there is no cross-wave reduction.
 constexpr int WIDE_NW = 8;
+// Rows it takes.  In bf16 the prompt GEMM takes over above 64: it splits the rows over more workgroups, where this
+// one holds all rows' X chunks in LDS and runs one workgroup per CU (8B shape, wide against prompt: 64 rows 134 / 141
+// us for the four GEMMs of a layer, 96 rows 196 / 159, 160 rows 287 / 218, 256 rows 425 / 235; 1B shape: 64 rows
+// 55 / 67, 96 rows 82 / 75, 160 rows 125 / 92).
+template <typename T> constexpr int WIDE_MAX_M = 256;
+template <> constexpr int WIDE_MAX_M<bf16> = 64;
 constexpr int WIDE_KC = 128;
 constexpr int MAX_WIDE_SWIGLU_SPLIT = 4;
 
@@ -1403,12 +1409,18 @@ static int gemm_wide(GemmArgs a, int max_split, int tag, Stream s, int* nsplit_o
       else                                                                                              \
         launch_k((k_gemm_wide<T, MTV, TNV, EPI, 1, NX>), grid, dim3(64 * WIDE_NW), 0, s, a);            \
     } while (0)
-    if (TN == 2) {
-      if (mt <= 2) HAM_WIDE(2, 2); else if (mt <= 4) HAM_WIDE(4, 2); else if (mt <= 8) HAM_WIDE(8, 2);
-      else if (mt <= 10) HAM_WIDE(10, 2); else HAM_WIDE(16, 2);
+    if (mt <= 2) {
+      if (TN == 2) HAM_WIDE(2, 2); else HAM_WIDE(2, 1);
+    } else if (mt <= 4) {
+      if (TN == 2) HAM_WIDE(4, 2); else HAM_WIDE(4, 1);
+    } else if constexpr (WIDE_MAX_M<T> > 64) {
+      if (TN == 2) {
+        if (mt <= 8) HAM_WIDE(8, 2); else if (mt <= 10) HAM_WIDE(10, 2); else HAM_WIDE(16, 2);
+      } else {
+        if (mt <= 8) HAM_WIDE(8, 1); else if (mt <= 10) HAM_WIDE(10, 1); else HAM_WIDE(16, 1);
+      }
     } else {
-      if (mt <= 2) HAM_WIDE(2, 1); else if (mt <= 4) HAM_WIDE(4, 1); else if (mt <= 8) HAM_WIDE(8, 1);
-      else if (mt <= 10) HAM_WIDE(10, 1); else HAM_WIDE(16, 1);
+      return -1;
     }
 #undef HAM_WIDE
     if (EPI == EPI_SWIGLU && nsplit > 1)
@@ -1423,9 +1435,9 @@ static int gemm_t(const GemmArgs& a0, int max_split, int tag, Stream s, int* nsp
   if (a.N % 32 != 0 || a.K % KB != 0 || a.M <= 0) return -1;
   if ((a.no.ss || a.rs.ss) && a.xsrc != XS_ACT) return -1;  // NormOut, RowScale: plain operand only
   *nsplit_out = 1;
-  if (a.xsrc == XS_NORMW) {  // normed X built by the batched GEMM itself (8 < M <= 256)
+  if (a.xsrc == XS_NORMW) {  // normed X built by the batched GEMM itself (8 < M <= WIDE_MAX_M)
     if constexpr (EPI == EPI_F32 || EPI == EPI_SWIGLU) {
-      if (a.M > 8 && a.M <= 256 && a.K % WIDE_KC == 0 && a.xs.x && a.xs.g && a.xs.ssw &&
+      if (a.M > 8 && a.M <= WIDE_MAX_M<T> && a.K % WIDE_KC == 0 && a.xs.x && a.xs.g && a.xs.ssw &&
           a.xs.nchw == (a.K + 255) / 256) {
         if (dry) return 0;
         return gemm_wide<T, EPI, true>(a, max_split, tag, s, nsplit_out);
@@ -1450,7 +1462,7 @@ static int gemm_t(const GemmArgs& a0, int max_split, int tag, Stream s, int* nsp
     // the row scale is applied by the skinny kernel of one 16-row tile only
     if (a.rs.ss && (a.M > NORM_OUT_MAX_ROWS || a.rs.n < 1 || a.rs.n > NORM_OUT_MAX_TILES)) return -1;
   }
-  if (a.M > 8 && a.M <= 256 && a.K % WIDE_KC == 0 && EPI != EPI_XMASK && EPI != EPI_OP)
+  if (a.M > 8 && a.M <= WIDE_MAX_M<T> && a.K % WIDE_KC == 0 && EPI != EPI_XMASK && EPI != EPI_OP)
     return gemm_wide<T, EPI>(a, max_split, tag, s, nsplit_out);
   if (a.M > 64) {
     if constexpr (EPI == EPI_ARGMAX) {

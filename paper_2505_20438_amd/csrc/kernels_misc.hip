@@ -140,6 +140,12 @@ int launch_norm_reduce(const NormArgs& a, Stream s) {
   return 0;
 }
 
+int launch_fold(const NormArgs& a, Stream s) {
+  if (a.R < 1 || a.R > 65535 || !a.ss || !a.part || a.nsplit < 1 || a.nsplit > NORM_MAXS) return -1;
+  launch_k(k_norm_reduce, dim3((a.d + 255) / 256, a.R), dim3(256), 0, s, a);
+  return 0;
+}
+
 int launch_rmsnorm(int dtype, const NormArgs& a, Stream s) {
   if (a.R <= 0) return 0;
   if (a.d > NORM_THREADS * NORM_MAXV || (a.part && (a.nsplit < 1 || a.nsplit > NORM_MAXS))) return -1;

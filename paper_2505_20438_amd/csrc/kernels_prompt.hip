@@ -265,25 +265,54 @@ __global__ __launch_bounds__(512, 2) void k_gemm_pp(GemmArgs a) {
   }
 }
 
+// Tile width and k-split of a launch: the pair with the least estimated time, in cycles at the 1.8 GHz that the matrix
+// cores keep under load (256 workgroups run at once, one per CU):
+//  rounds of workgroups x (stages x cycles per stage + a fixed cost for the first loads, the exchange and the stores),
+//  at least what the weights take to arrive; split results are written and read again as fp32 partials.
+// Measured: 1,310 cycles per stage of the 256-column tile, 850 of the 128-column tile, 12,000 fixed (from the times of
+// k-ranges of 2,048 to 14,336), 3,000 bytes per cycle.
+struct PromptPlan {
+  int bn, nsplit;
+};
+static PromptPlan prompt_plan(int M, int N, int K, int most) {
+  const double fixed = 12000, bytes_per_cycle = 3000;
+  const int gy = (M + PP<256>::BM - 1) / PP<256>::BM, nfr = K / PP<256>::KB;
+  PromptPlan best{256, 1};
+  double best_t = 1e30;
+  for (int bn = 256; bn >= 128; bn -= 128)
+    for (int ns = 1; ns <= most; ++ns) {
+      if (ns > 1 && nfr / ns < 8) break;
+      const long wgs = (long)((N + bn - 1) / bn) * gy * ns;
+      const double rounds = (double)((wgs + 255) / 256), stages = (double)((nfr + ns - 1) / ns);
+      const double t = std::max(rounds * (stages * (bn == 256 ? 1310 : 850) + fixed), (double)N * K * 2 / bytes_per_cycle) +
+                       (ns > 1 ? (double)M * N * 4 * 2 * ns / bytes_per_cycle : 0);
+      if (t < best_t * 0.97) {  // a split or a narrow tile has to gain something
+        best_t = t;
+        best = PromptPlan{bn, ns};
+      }
+    }
+  return best;
+}
+
 template <int EPI>
-static int prompt_t(const GemmArgs& a, Stream s) {
+static int prompt_t(const GemmArgs& a, int max_split, Stream s, int* nsplit) {
+  // a split needs room for its partials; SwiGLU needs whole sums
+  const long room = a.part && a.part_cap > 0 ? a.part_cap / ((long)a.M * a.N) : 1;
+  const int most = EPI == EPI_SWIGLU ? 1 : (int)std::max(1L, std::min((long)max_split, room));
+  const PromptPlan p = prompt_plan(a.M, a.N, a.K, most);
   const int gy = (a.M + 127) / 128;
-  // 256-column tiles (half the operand reads from LDS per product of the narrow ones) while they give half the CUs one
-  if ((long)((a.N + 255) / 256) * gy >= 128)
-    launch_k((k_gemm_pp<EPI, 256>), dim3((a.N + 255) / 256 * gy), dim3(512), 0, s, a);
-  else
-    launch_k((k_gemm_pp<EPI, 128>), dim3((a.N + 127) / 128 * gy), dim3(512), 0, s, a);
+  *nsplit = p.nsplit;
+  if (p.bn == 256) launch_k((k_gemm_pp<EPI, 256>), dim3((a.N + 255) / 256 * gy, p.nsplit), dim3(512), 0, s, a);
+  else launch_k((k_gemm_pp<EPI, 128>), dim3((a.N + 127) / 128 * gy, p.nsplit), dim3(512), 0, s, a);
   return 0;
 }
 
 int launch_gemm_prompt(int epi, const GemmArgs& a, int max_split, Stream s, int* nsplit) {
-  (void)max_split;
   if (a.M < 1 || a.N % 32 != 0 || a.K % 32 != 0 || a.ldo % 4 != 0) return -1;
-  *nsplit = 1;
   switch (epi) {
-    case EPI_F32: return prompt_t<EPI_F32>(a, s);
-    case EPI_RESID: return prompt_t<EPI_RESID>(a, s);
-    case EPI_SWIGLU: return prompt_t<EPI_SWIGLU>(a, s);
+    case EPI_F32: return prompt_t<EPI_F32>(a, max_split, s, nsplit);
+    case EPI_RESID: return prompt_t<EPI_RESID>(a, max_split, s, nsplit);
+    case EPI_SWIGLU: return prompt_t<EPI_SWIGLU>(a, max_split, s, nsplit);
     default: return -1;
   }
 }

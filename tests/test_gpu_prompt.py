@@ -49,6 +49,6 @@ def _check(shp, B, P, rows, seed=301):
 
 
 @pytest.mark.parametrize("dtype", [BF16, F32])
-@pytest.mark.parametrize("prompt", [257, 300, 513])
+@pytest.mark.parametrize("prompt", [65, 130, 257, 300, 513])   # the batched GEMM's last row count, whole and cut tiles
 def test_prompt_rows_past_a_tile(dtype, prompt):
     _check(dataclasses.replace(EDGES, dtype=dtype), 1, prompt, [0])
