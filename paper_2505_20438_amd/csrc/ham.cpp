@@ -124,7 +124,8 @@ Layout make_layout(const ham_config* c) {
     y.ctx_l[i] = i >= y.C ? -1
                  : c->n_ctx_layers > 0 ? c->ctx_layers[i]
                                        : (int)(((long long)(i + 1) * y.L + y.C - 1) / y.C);
-  y.Tc = std::min(y.P, 2048);
+  // rows of one prefill chunk: the prompts of a batch run as one stream of rows
+  y.Tc = (int)std::min((long long)y.P * y.B, 2048ll);
   y.rows_dec = y.B * (y.C + 1);
   y.rows_max = std::max(y.Tc, std::max(y.rows_dec, 5 * y.B));
   y.Nmax = std::max(std::max(y.QKV, 2 * y.F), std::max(y.d, 3 * y.HD));
@@ -615,7 +616,7 @@ constexpr int LAST_ROWS_MIN = 64;
 int run_layer(ham_model* m, int j, int R, const RowMap& rm, float*& x, bool prefill, void* Kc, void* VTc,
               long long sb, long long sh, int S, int attn_split, const int* gate, int gate_n, Pending& pend,
               float* ctx_prev, int ldctx, int kv_visible, const StepAttn* step, const float* g_next = nullptr,
-              float* ctx_out = nullptr, bool last_rows = false, bool kv_only = false, bool last_row = false) {
+              float* ctx_out = nullptr, bool last_rows = false, bool kv_only = false) {
   const Layout& y = m->y;
   const int dt = dtype_of(m);
   hipStream_t s = m->s;
@@ -682,23 +683,6 @@ int run_layer(ham_model* m, int j, int R, const RowMap& rm, float*& x, bool pref
     aa.rm = r1;
     R = B;
     x = xc;
-  }
-  if (last_row) {
-    // The prompt's last chunk at the last base layer: every row's K and V are
-    // appended, but the outputs are read only at the last row (the first
-    // decision and the context rows), so attention (split over that row's
-    // slots) and tail run on it alone
-    if (!prefill || rm.mode != ROWS_PREFILL) return fail(HAM_EINVAL, "last-row prefill layer");
-    RowMap r1 = rm;
-    r1.t0 = rm.t0 + R - 1;
-    aa.q = m->WS<char>(y.q) + (size_t)(R - 1) * y.HD * 4;  // 4 bytes per activation value
-    aa.R = 1;
-    aa.rm = r1;
-    aa.nsplit = attn_splits_for(dt, 1, y.Hk, r1.t0 + 1);
-    if (launch_attn_decode(dt, aa, s) != 0) return fail(HAM_EINVAL, "attention shape");
-    float* xl = x + (size_t)(R - 1) * y.d;
-    if (int rc = layer_tail(m, j, 1, xl, split, gate, gate_n, pend, gk)) return rc;
-    return fold_pending(m, xl, 1, pend);
   }
   m->pbegin(base ? HAM_PROF_ATTN : -1, (double)kv_visible * y.Hk * y.hd * 2 * y.es);
   const int arc = prefill ? launch_attn_prefill(dt, aa, s) : launch_attn_decode(dt, aa, s);
@@ -966,43 +950,66 @@ int prefill_common(ham_model* m, int32_t batch, int32_t T, const int32_t* d_prom
   float* x = m->WS<float>(y.x);
   float* ctx = m->WS<float>(y.ctx);
   const long long sb = (long long)y.Hk * y.S * y.hd, sh = (long long)y.S * y.hd;
-  for (int b = 0; b < batch; ++b) {
-    for (int t0 = 0; t0 < T; t0 += y.Tc) {
-      const int R = std::min(y.Tc, T - t0);
-      const bool last = t0 + R == T;
-      GatherArgs g{};
-      if (d_embeds) g.rows = d_embeds + ((size_t)b * T + t0) * y.d;
-      else g.ids = d_prompt + (size_t)b * T + t0;
-      g.R = R; g.E = m->W<char>(y.E); g.d = y.d; g.V = y.V;
-      g.x = xp; g.ldx = y.d; g.err = m->sp.err + b;
-      launch_gather_rows(dt, g, s);
-      RowMap rm{};
-      rm.mode = ROWS_PREFILL; rm.b = b; rm.t0 = t0; rm.pos = d_positions; rm.ldpos = T; rm.st = m->sp;
-      Pending pend;  // a layer's split down projection, folded in by the next layer's norm
-      for (int l = 0; l < y.L; ++l) {
-        // the last layer's outputs are read only at the prompt's last row (the
-        // decision and the context rows): earlier chunks append its K and V
-        // only, the last chunk runs attention and tail on that row alone
-        const bool kv_only = !last && l == y.L - 1;
-        const bool last_row = last && l == y.L - 1 && R > 1;
-        int rc = run_layer(m, l, R, rm, xp, true, m->st + y.Kc + l * y.kv_layer, m->st + y.VTc + l * y.kv_layer,
-                           sb, sh, y.S, 1, nullptr, 0, pend, nullptr, 0, 0, nullptr, nullptr, nullptr, false, kv_only,
-                           last_row);
-        if (rc) return rc;
-        bool read_here = last && l == y.L - 1;  // the output rows are read before another norm
-        if (last)
-          for (int c = 0; c < y.C; ++c) read_here |= y.ctx_l[c] == l + 1;
-        if (read_here && (rc = fold_pending(m, xp, R, pend))) return rc;
-        if (last)
-          for (int c = 0; c < y.C; ++c)
-            if (y.ctx_l[c] == l + 1)
-              launch_copy_row(xp + (size_t)(R - 1) * y.d, ctx + ((size_t)b * y.C + c) * y.d, y.d, s);
+  // The batch's inputs are one stream of batch * T rows (row g: input g % T of sequence g / T), in chunks of equal
+  // size: a chunk takes in the end of one prompt and the next ones, so short prompts share the pass over the weights
+  // (16 prompts of 77 rows, 1B shape: one sequence at a time 28.0 ms), and earlier chunks hold every row that a row attends to.
+  const long long total = (long long)batch * T;
+  const long long nchunk = (total + y.Tc - 1) / y.Tc;
+  const int step = (int)std::min<long long>(y.Tc, rup((int)((total + nchunk - 1) / nchunk), 128));
+  for (long long g0 = 0; g0 < total; g0 += step) {
+    const int R = (int)std::min<long long>(step, total - g0);
+    GatherArgs g{};
+    if (d_embeds) g.rows = d_embeds + (size_t)g0 * y.d;
+    else g.ids = d_prompt + g0;
+    g.R = R; g.E = m->W<char>(y.E); g.d = y.d; g.V = y.V;
+    g.x = xp; g.ldx = y.d; g.err = m->sp.err; g.g0 = g0; g.T = T;
+    launch_gather_rows(dt, g, s);
+    RowMap rm{};
+    rm.mode = ROWS_PREFILL; rm.g0 = g0; rm.T = T; rm.pos = d_positions; rm.st = m->sp;
+    // sequences b0 .. b0 + nb - 1 end in this chunk, the first at row `end0`
+    const int b0 = (int)(g0 / T), nb = (int)((g0 + R) / T) - b0;
+    const size_t end0 = (size_t)((long long)(b0 + 1) * T - 1 - g0);
+    Pending pend;  // a layer's split down projection, folded in by the next layer's norm
+    for (int l = 0; l < y.L; ++l) {
+      // the last layer's outputs are read only at the prompts' last rows: here it appends K and V of every row, and
+      // those rows' residuals and queries are kept for one launch over all sequences after the last chunk
+      const bool kv_only = l == y.L - 1;
+      int rc = run_layer(m, l, R, rm, xp, true, m->st + y.Kc + l * y.kv_layer, m->st + y.VTc + l * y.kv_layer, sb, sh,
+                         y.S, 1, nullptr, 0, pend, nullptr, 0, 0, nullptr, nullptr, nullptr, false, kv_only);
+      if (rc) return rc;
+      if (nb == 0) continue;
+      if (kv_only) {
+        if (launch_copy_rows(xp + end0 * y.d, (long long)T * y.d, x + (size_t)b0 * y.d, y.d, nb, y.d, s) ||
+            launch_copy_rows(m->WS<float>(y.q) + end0 * y.HD, (long long)T * y.HD,  // 4 bytes per activation value
+                             m->WS<float>(y.emb_o) + (size_t)b0 * y.HD, y.HD, nb, y.HD, s))
+          return fail(HAM_EINVAL, "row copy shape");
+        continue;
       }
-      if (last) launch_copy_row(xp + (size_t)(R - 1) * y.d, x + (size_t)b * y.d, y.d, s);
+      for (int c = 0; c < y.C; ++c)
+        if (y.ctx_l[c] == l + 1) {
+          if ((rc = fold_pending(m, xp, R, pend))) return rc;
+          if (launch_copy_rows(xp + end0 * y.d, (long long)T * y.d, ctx + ((size_t)b0 * y.C + c) * y.d,
+                               (long long)y.C * y.d, nb, y.d, s))
+            return fail(HAM_EINVAL, "row copy shape");
+        }
     }
   }
-  Pending none;
-  int rc = decode_tail(m, none, nullptr, x, d_out_tokens, d_out_lens);
+  // the last layer's attention and tail, one row per sequence (kv_len = T since the set-up)
+  const int l = y.L - 1;
+  AttnArgs aa{};
+  aa.q = m->WS<char>(y.emb_o); aa.ldq = y.HD; aa.K = m->st + y.Kc + l * y.kv_layer; aa.VT = m->st + y.VTc + l * y.kv_layer;
+  aa.sb = sb; aa.sh = sh; aa.S = y.S; aa.H = y.H; aa.Hkv = y.Hk; aa.hd = y.hd; aa.R = batch;
+  aa.nsplit = attn_splits_for(dt, batch, y.Hk, T); aa.o = m->WS<char>(y.ao); aa.ldo = y.HD;
+  aa.part = m->WS<float>(y.apart); aa.rm.mode = ROWS_DECODE; aa.rm.st = m->sp;
+  if (launch_attn_decode(dt, aa, s) != 0) return fail(HAM_EINVAL, "attention shape");
+  Pending pend;
+  const auto no_prof = [](int) { return -1; };
+  int rc = layer_tail(m, l, batch, x, MAX_GEMM_SPLIT, nullptr, 0, pend, no_prof);
+  if (rc) return rc;
+  float* ctx_last = nullptr;  // context slot of the last layer's output, captured by the decision's norm
+  for (int c = 0; c < y.C; ++c)
+    if (y.ctx_l[c] == y.L) ctx_last = ctx + (size_t)c * y.d;
+  rc = decode_tail(m, pend, ctx_last, x, d_out_tokens, d_out_lens);
   if (rc) return rc;
   HIP_TRY(hipGetLastError());
   m->steps_done = 0;

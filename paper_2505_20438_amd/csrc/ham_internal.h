@@ -62,9 +62,8 @@ struct SeqPtrs {
 enum RowMode { ROWS_PREFILL = 0, ROWS_DECODE = 1, ROWS_MICRO1 = 2, ROWS_MICROK = 3 };
 struct RowMap {
   int mode;
-  int b;        // PREFILL: the sequence
-  int t0;       // PREFILL: slot of row 0
-  const int* pos; int ldpos;  // PREFILL: RoPE position of slot t at pos[b*ldpos + t] (null: position = slot)
+  long long g0; int T;  // PREFILL: row r is row g0 + r of the batch's stream, input g % T of sequence g / T
+  const int* pos;       // PREFILL: RoPE position of stream row g at pos[g] (null: position = slot)
   int C;        // MICRO*: context rows
   int k;        // MICROK: micro step index (>= 2)
   SeqPtrs st;

@@ -21,6 +21,8 @@
 //
 // Softmax statistics are fp32.  For bf16 caches the probabilities enter the
 // bf16 product as a hi + lo pair (about 16 significant bits).
+#include <algorithm>
+
 #include "device_common.h"
 #include "ham_internal.h"
 #include "rows.h"
@@ -581,9 +583,9 @@ __device__ __forceinline__ void pfa_wait_vm_lgkm0() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
 }
 
-// Prefill: causal attention of a prompt chunk (rows of mode PREFILL: slots
-// t0 + r of one sequence).  One workgroup of PF_NW waves per (row chunk, kv
-// head): wave w takes q-head kvh*grp + w % grp and PF_RT tiles of 16 rows from
+// Prefill: causal attention of a prompt chunk (rows of mode PREFILL, of one
+// or more sequences).  One workgroup of PF_NW waves per (row chunk of a
+// sequence, kv head): wave w takes q-head kvh*grp + w % grp and PF_RT tiles of 16 rows from
 // row 16*PF_RT*(w / grp) of the chunk, so a chunk is 16*PF_RT*(PF_NW / grp)
 // rows; each key block a wave reads from LDS serves all its row tiles.  Key
 // blocks land in LDS straight from memory (global_load_lds_dwordx4), PF_NBL per
@@ -603,15 +605,19 @@ __global__ __launch_bounds__(64 * PF_NW) void k_attn_prefill(AttnArgs a) {
   const int grp = a.H / a.Hkv, nrg = PF_NW / grp, RB = 16 * PF_RT * nrg;
   const int jh = w % grp, rg = w / grp;
   const int h = kvh * grp + jh;
-  const int chunk0 = blockIdx.x * RB;
-  if (chunk0 >= a.R) return;  // the same for every wave of the workgroup
-  const RowInfo r0 = row_info(a.rm, chunk0);
-  const int wg_end = r0.slot + min(RB, a.R - chunk0);  // keys [0, wg_end)
+  // rows [lo, hi) of the launch belong to sequence b; the blocks with the most keys start first
+  const int b = (int)(a.rm.g0 / a.rm.T) + blockIdx.z;
+  const long long first = (long long)b * a.rm.T - a.rm.g0;  // launch row of the sequence's slot 0
+  const int lo = (int)max(first, 0ll), hi = (int)min(first + a.rm.T, (long long)a.R);
+  const int chunk0 = lo + (int)(gridDim.x - 1 - blockIdx.x) * RB;
+  if (chunk0 >= hi) return;  // the same for every wave of the workgroup
+  const int slot0 = (int)(chunk0 - first);
+  const int wg_end = slot0 + min(RB, hi - chunk0);  // keys [0, wg_end)
   const int row0 = chunk0 + rg * 16 * PF_RT;
-  const bool rows_ok = rg < nrg && row0 < a.R;          // waves past the q-heads only load
-  const int wave_end = rows_ok ? r0.slot + (row0 - chunk0) + min(16 * PF_RT, a.R - row0) : 0;
-  const T* Kb = (const T*)a.K + r0.b * a.sb + kvh * a.sh;
-  const T* Vb = (const T*)a.VT + r0.b * a.sb + kvh * a.sh;
+  const bool rows_ok = rg < nrg && row0 < hi;           // waves past the q-heads only load
+  const int wave_end = rows_ok ? slot0 + (row0 - chunk0) + min(16 * PF_RT, hi - row0) : 0;
+  const T* Kb = (const T*)a.K + b * a.sb + kvh * a.sh;
+  const T* Vb = (const T*)a.VT + b * a.sb + kvh * a.sh;
 
   u4 qf[PF_RT][NF], ql[PF_RT][NF];
   int limit[PF_RT], tile_end[PF_RT];
@@ -619,7 +625,7 @@ __global__ __launch_bounds__(64 * PF_NW) void k_attn_prefill(AttnArgs a) {
 #pragma unroll
   for (int t = 0; t < PF_RT; ++t) {
     const int trow = row0 + 16 * t, qrow = trow + r16;
-    const bool qok = rows_ok && qrow < a.R;
+    const bool qok = rows_ok && qrow < hi;
     const T* qp = (const T*)a.q + (size_t)(qok ? qrow : 0) * a.ldq * PL + (size_t)h * HD + g * EPL;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
@@ -627,8 +633,8 @@ __global__ __launch_bounds__(64 * PF_NW) void k_attn_prefill(AttnArgs a) {
       ql[t][f] = (Act<T>::SPLIT && qok) ? ld16(qp + a.ldq + f * KB) : zero16();
     }
     // causal: the row at slot s sees slots [0, s]
-    limit[t] = qok ? r0.slot + (qrow - chunk0) + 1 : 0;
-    tile_end[t] = (rows_ok && trow < a.R) ? r0.slot + (trow - chunk0) + min(16, a.R - trow) : 0;
+    limit[t] = qok ? slot0 + (qrow - chunk0) + 1 : 0;
+    tile_end[t] = (rows_ok && trow < hi) ? slot0 + (trow - chunk0) + min(16, hi - trow) : 0;
   }
 
   const int nblk = (wg_end + KB - 1) / KB, nst = (nblk + PF_NBL - 1) / PF_NBL;
@@ -711,7 +717,7 @@ __global__ __launch_bounds__(64 * PF_NW) void k_attn_prefill(AttnArgs a) {
       const int jr = 4 * g + i;  // query row within the tile
       const float lj = __shfl(lrun[t], jr, WAVE);
       const int row = row0 + 16 * t + jr;
-      if (row < a.R) {
+      if (row < hi) {
         const float inv = lj > 0.f ? 1.0f / lj : 0.f;
 #pragma unroll
         for (int dt = 0; dt < ND; ++dt) Act<T>::put(a.o, row, a.ldo, h * HD + r16 + dt * 16, o[t][dt][i] * inv);
@@ -733,7 +739,9 @@ static int prefill_t(const AttnArgs& a, Stream s) {
   const int grp = a.H / a.Hkv;
   if (grp < 1 || grp > PF_NW) return -1;
   const int rb = 16 * PF_RT * (PF_NW / grp);  // rows per workgroup
-  dim3 grid((a.R + rb - 1) / rb, a.Hkv);
+  // sequences that have rows in the launch, and the row blocks of the longest share
+  const long long b0 = a.rm.g0 / a.rm.T, b1 = (a.rm.g0 + a.R - 1) / a.rm.T;
+  dim3 grid((std::min(a.R, a.rm.T) + rb - 1) / rb, a.Hkv, (unsigned)(b1 - b0 + 1));
   if (a.hd == 64) launch_k((k_attn_prefill<T, 64>), grid, dim3(64 * PF_NW), 0, s, a);
   else if (a.hd == 128) launch_k((k_attn_prefill<T, 128>), grid, dim3(64 * PF_NW), 0, s, a);
   else return -1;
@@ -773,7 +781,7 @@ int launch_attn_decode(int dtype, const AttnArgs& a, Stream s) {
   return dtype == 1 ? decode_t<bf16>(a, s) : decode_t<float>(a, s);
 }
 int launch_attn_prefill(int dtype, const AttnArgs& a, Stream s) {
-  if (a.H % a.Hkv != 0 || a.S % 64 != 0 || a.rm.mode != ROWS_PREFILL) return -1;
+  if (a.H % a.Hkv != 0 || a.S % 64 != 0 || a.rm.mode != ROWS_PREFILL || a.rm.T < 1 || a.R < 1) return -1;
   return dtype == 1 ? prefill_t<bf16>(a, s) : prefill_t<float>(a, s);
 }
 

@@ -36,7 +36,7 @@ struct PrefillArgs {
 struct GatherArgs {
   const int* ids; int R; const void* E; int d, V; float* x; int ldx;
   const float* rows;                // if set: copy fp32 rows [R][d] from here instead of gathering E rows
-  int* err;                         // set (bit 2) if an id is out of range
+  int* err; long long g0; int T;    // err of row r's sequence, (g0 + r) / T: set (bit 2) if its id is out of range
 };
 
 struct GenArgs {
@@ -47,7 +47,6 @@ void launch_macro_begin(int dtype, const MacroArgs& a, Stream s);
 void launch_embed_attn(int dtype, const EmbedAttnArgs& a, Stream s);
 void launch_prefill_begin(const PrefillArgs& a, Stream s);
 void launch_gather_rows(int dtype, const GatherArgs& a, Stream s);
-void launch_copy_row(const float* src, float* dst, int d, Stream s);
 // R rows of d fp32 values from src (pitch ld_src floats) to dst (pitch ld_dst); 16-byte aligned rows
 int launch_copy_rows(const float* src, long long ld_src, float* dst, long long ld_dst, int R, int d, Stream s);
 void launch_gen_normal(int dtype, const GenArgs& a, Stream s);

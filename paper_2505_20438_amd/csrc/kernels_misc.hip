@@ -408,15 +408,11 @@ __global__ __launch_bounds__(256) void k_gather_rows(GatherArgs a) {
   }
   int t = a.ids[r];
   if (t < 0 || t >= a.V) {  // caller-provided id out of range: flag it, read row 0
-    if (threadIdx.x == 0) atomicOr(a.err, 2);
+    if (threadIdx.x == 0) atomicOr(a.err + (a.g0 + r) / a.T, 2);
     t = 0;
   }
   const T* E = (const T*)a.E;
   for (int i = threadIdx.x; i < a.d; i += 256) a.x[(size_t)r * a.ldx + i] = to_f<T>(E[(size_t)t * a.d + i]);
-}
-
-__global__ __launch_bounds__(256) void k_copy_row(const float* src, float* dst, int d) {
-  for (int i = threadIdx.x; i < d; i += 256) dst[i] = src[i];
 }
 
 // dst row r = src row r (rows of d floats, d % 4 == 0, at their own pitches)
@@ -480,9 +476,6 @@ void launch_prefill_begin(const PrefillArgs& a, Stream s) {
 }
 void launch_gather_rows(int dtype, const GatherArgs& a, Stream s) {
   HAM_T_LAUNCH(dtype, k_gather_rows, dim3(a.R), dim3(256), s, a);
-}
-void launch_copy_row(const float* src, float* dst, int d, Stream s) {
-  launch_k(k_copy_row, dim3(1), dim3(256), 0, s, src, dst, d);
 }
 int launch_copy_rows(const float* src, long long ld_src, float* dst, long long ld_dst, int R, int d, Stream s) {
   if (R < 0 || d % 4 != 0 || ld_src % 4 != 0 || ld_dst % 4 != 0) return -1;

@@ -12,13 +12,15 @@ struct RowInfo {
 __device__ __forceinline__ RowInfo row_info(const RowMap& rm, int r) {
   RowInfo ri;
   switch (rm.mode) {
-    case ROWS_PREFILL:  // one slot per input row, causal; position = slot unless given
-      ri.b = rm.b;
-      ri.slot = rm.t0 + r;
-      ri.pos = rm.pos ? rm.pos[(size_t)rm.b * rm.ldpos + ri.slot] : ri.slot;
+    case ROWS_PREFILL: {  // one slot per input row, causal; position = slot unless given
+      const long long g = rm.g0 + r;
+      ri.b = (int)(g / rm.T);
+      ri.slot = (int)(g - (long long)ri.b * rm.T);
+      ri.pos = rm.pos ? rm.pos[g] : ri.slot;
       ri.n_valid = ri.slot + 1;
       ri.enabled = 1;
       break;
+    }
     case ROWS_DECODE:  // one fused input per running sequence, at its group's last position
       ri.b = r;
       ri.slot = rm.st.cur_slot[r];

@@ -28,21 +28,24 @@ def _check(shp, B, P, rows, seed=301):
     assert torch.cuda.is_available(), "GPU tests need a GPU"
     from paper_2505_20438_amd import ham
     prompts = synth.prompt_ids(seed + 1, B, P, shp.vocab)
-    sched = synth.group_schedule(seed + 2, B, 2, 4)
+    sched = 1 + (np.arange(B, dtype=np.int32)[:, None] + np.array([[3, 0]], dtype=np.int32)) % 4   # 4, 1, 2, 3, ...
     om = OracleHam(shp, seed)
     rt = ham.HamRuntime(config_for(shp, B, P, 1), seed)
-    teacher = [[[(7 * b + j) % shp.vocab for j in range(sched[b, s])] for s in range(2)] for b in range(B)]
+    orc, caches = {}, {}
+    for b in rows:
+        orc[b] = om.generate(prompts[b], 0, 0, forced=lambda st, b=b: int(sched[b, st]), record=True)
+        caches[b] = om.last_caches
+    teacher = [orc[b].groups if b in orc else [[(7 * b + j) % shp.vocab for j in range(sched[b, 0])]] for b in range(B)]
     res = run_gpu(rt, prompts, [0] * B, 0, sched, teacher=teacher, debug_steps=1)
     tol = TOL[shp.dtype]
     kv = [[t.cpu().numpy().astype(np.float64) for t in rt.kv_cache(l, P)] for l in range(shp.n_layers)]
     for b in rows:
-        o = om.generate(prompts[b], 0, 0, forced=lambda st: 1, record=True)
-        dec = o.decisions[0]
-        assert np.max(np.abs(res.logits[(b, 0, 0)] - dec.logits)) <= tol, b
-        assert np.max(np.abs(res.hidden[(b, 0, 0)] - dec.h)) <= tol, b
+        for dec in orc[b].decisions:   # the first from the base model, the others through the context rows
+            assert np.max(np.abs(res.logits[(b, 0, dec.k)] - dec.logits)) <= tol, (b, dec.k)
+            assert np.max(np.abs(res.hidden[(b, 0, dec.k)] - dec.h)) <= tol, (b, dec.k)
         for l in range(shp.n_layers):
             for i, name in enumerate("KV"):
-                ref = np.transpose(om.last_caches[l][i], (1, 0, 2))
+                ref = np.transpose(caches[b][l][i], (1, 0, 2))
                 err = np.max(np.abs(kv[l][i][b] - ref), axis=(0, 2)) / np.max(np.abs(ref))
                 assert err.max() <= tol, (b, l, name, int(err.argmax()), float(err.max()))
     assert all(s["kv_len"] == P and s["device_error"] == 0 for s in rt.kv_stats())
@@ -52,3 +55,15 @@ def _check(shp, B, P, rows, seed=301):
 @pytest.mark.parametrize("prompt", [65, 130, 257, 300, 513])   # the batched GEMM's last row count, whole and cut tiles
 def test_prompt_rows_past_a_tile(dtype, prompt):
     _check(dataclasses.replace(EDGES, dtype=dtype), 1, prompt, [0])
+
+
+# Batches run as one stream of rows in chunks: several prompts in a chunk, prompts cut by a chunk's end (1100 rows: 3
+# chunks of 1152 for 3 prompts; 700: 2 of 1792), chunks that end exactly at a prompt's end, one-token prompts.
+@pytest.mark.parametrize("shape,batch,prompt,rows", [
+    (EDGES, 5, 1, [0, 4]), (EDGES, 3, 77, [0, 1, 2]), (EDGES, 17, 16, [0, 8, 16]), (EDGES, 4, 64, [0, 3]),
+    (EDGES, 3, 1100, [0, 1, 2]), (EDGES, 5, 700, [1, 2, 4]), (EDGES, 2, 2048, [1]),
+    (dataclasses.replace(EDGES, n_layers=1), 3, 70, [0, 2]),
+    (dataclasses.replace(EDGES, n_layers=3, ctx_layer_set=(1, 2)), 3, 70, [0, 2]),
+    (dataclasses.replace(EDGES, dtype=F32), 3, 77, [0, 1, 2]), (dataclasses.replace(EDGES, dtype=F32), 3, 1100, [1])])
+def test_prompts_share_chunks(shape, batch, prompt, rows):
+    _check(shape, batch, prompt, rows)
