@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libham.so")
 BUILD = os.path.join(HERE, "_build")
-SOURCES = ["kernels_gemm.hip", "kernels_prompt.hip", "kernels_attn.hip", "kernels_misc.hip", "ham.cpp"]
+SOURCES = ["kernels_gemm.hip", "kernels_prompt.hip", "kernels_attn.hip", "kernels_attn_prompt.hip", "kernels_misc.hip", "ham.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 # packed fp32 VALU forms are kept out of every kernel
@@ -46,7 +46,7 @@ def build(verbose: bool = True, incremental: bool = False) -> str:
     """Compile every source (``incremental``: only those whose object is older
     than the source or a header) and link the library."""
     os.makedirs(BUILD, exist_ok=True)
-    with ThreadPoolExecutor(min(5, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(min(6, len(SOURCES))) as ex:
         objs = list(ex.map(lambda src: _compile(src, incremental), SOURCES))
     tmp = OUT + ".tmp"
     cmd = [HIPCC, "-shared", f"--offload-arch={ARCH}", "-o", tmp, *objs]

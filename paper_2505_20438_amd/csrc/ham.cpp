@@ -962,10 +962,10 @@ int prefill_common(ham_model* m, int32_t batch, int32_t T, const int32_t* d_prom
     if (d_embeds) g.rows = d_embeds + (size_t)g0 * y.d;
     else g.ids = d_prompt + g0;
     g.R = R; g.E = m->W<char>(y.E); g.d = y.d; g.V = y.V;
-    g.x = xp; g.ldx = y.d; g.err = m->sp.err; g.g0 = g0; g.T = T;
+    g.x = xp; g.ldx = y.d; g.err = m->sp.err; g.b0 = (int)(g0 / T); g.s0 = (int)(g0 % T); g.T = T;
     launch_gather_rows(dt, g, s);
     RowMap rm{};
-    rm.mode = ROWS_PREFILL; rm.g0 = g0; rm.T = T; rm.pos = d_positions; rm.st = m->sp;
+    rm.mode = ROWS_PREFILL; rm.b0 = (int)(g0 / T); rm.s0 = (int)(g0 % T); rm.T = T; rm.pos = d_positions; rm.st = m->sp;
     // sequences b0 .. b0 + nb - 1 end in this chunk, the first at row `end0`
     const int b0 = (int)(g0 / T), nb = (int)((g0 + R) / T) - b0;
     const size_t end0 = (size_t)((long long)(b0 + 1) * T - 1 - g0);

@@ -62,8 +62,8 @@ struct SeqPtrs {
 enum RowMode { ROWS_PREFILL = 0, ROWS_DECODE = 1, ROWS_MICRO1 = 2, ROWS_MICROK = 3 };
 struct RowMap {
   int mode;
-  long long g0; int T;  // PREFILL: row r is row g0 + r of the batch's stream, input g % T of sequence g / T
-  const int* pos;       // PREFILL: RoPE position of stream row g at pos[g] (null: position = slot)
+  int b0, s0, T;   // PREFILL: rows follow each other through sequences of T inputs; row 0 is input s0 of sequence b0
+  const int* pos;  // PREFILL: RoPE position of input t of sequence b at pos[b*T + t] (null: position = slot)
   int C;        // MICRO*: context rows
   int k;        // MICROK: micro step index (>= 2)
   SeqPtrs st;
@@ -209,6 +209,7 @@ int skinny_tiles(int N);  // column tiles (argmax partials per row) of a skinny 
 int launch_split_reduce(int dtype, int epi, const GemmArgs& a, Stream s);
 int launch_attn_decode(int dtype, const AttnArgs& a, Stream s);
 int launch_attn_prefill(int dtype, const AttnArgs& a, Stream s);
+int launch_attn_prompt(const AttnArgs& a, Stream s);  // the same in bf16 (launch_attn_prefill takes it by itself)
 int launch_attn_step(int dtype, const AttnStepArgs& a, Stream s);
 int attn_step_max_qkv_split();  // most split-K partials of the projection the step kernel sums
 

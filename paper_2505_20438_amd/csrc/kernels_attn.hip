@@ -17,7 +17,8 @@
 //   the log-sum-exp rule in split order.  Used for base decode (ragged kv_len per sequence) and the micro
 //   decoder's local cache.
 // k_attn_prefill: the q-heads of a kv head over 16-row groups of a prompt chunk,
-//   key blocks shared through LDS, causal.
+//   key blocks shared through LDS, causal (fp32 models; bf16 prompts run
+//   kernels_attn_prompt.hip).
 //
 // Softmax statistics are fp32.  For bf16 caches the probabilities enter the
 // bf16 product as a hi + lo pair (about 16 significant bits).
@@ -606,12 +607,12 @@ __global__ __launch_bounds__(64 * PF_NW) void k_attn_prefill(AttnArgs a) {
   const int jh = w % grp, rg = w / grp;
   const int h = kvh * grp + jh;
   // rows [lo, hi) of the launch belong to sequence b; the blocks with the most keys start first
-  const int b = (int)(a.rm.g0 / a.rm.T) + blockIdx.z;
-  const long long first = (long long)b * a.rm.T - a.rm.g0;  // launch row of the sequence's slot 0
-  const int lo = (int)max(first, 0ll), hi = (int)min(first + a.rm.T, (long long)a.R);
+  const int b = a.rm.b0 + blockIdx.z;
+  const int first = (int)blockIdx.z * a.rm.T - a.rm.s0;  // launch row of the sequence's slot 0
+  const int lo = max(first, 0), hi = min(first + a.rm.T, a.R);
   const int chunk0 = lo + (int)(gridDim.x - 1 - blockIdx.x) * RB;
   if (chunk0 >= hi) return;  // the same for every wave of the workgroup
-  const int slot0 = (int)(chunk0 - first);
+  const int slot0 = chunk0 - first;
   const int wg_end = slot0 + min(RB, hi - chunk0);  // keys [0, wg_end)
   const int row0 = chunk0 + rg * 16 * PF_RT;
   const bool rows_ok = rg < nrg && row0 < hi;           // waves past the q-heads only load
@@ -740,8 +741,8 @@ static int prefill_t(const AttnArgs& a, Stream s) {
   if (grp < 1 || grp > PF_NW) return -1;
   const int rb = 16 * PF_RT * (PF_NW / grp);  // rows per workgroup
   // sequences that have rows in the launch, and the row blocks of the longest share
-  const long long b0 = a.rm.g0 / a.rm.T, b1 = (a.rm.g0 + a.R - 1) / a.rm.T;
-  dim3 grid((std::min(a.R, a.rm.T) + rb - 1) / rb, a.Hkv, (unsigned)(b1 - b0 + 1));
+  const int nseq = (a.rm.s0 + a.R - 1) / a.rm.T + 1;
+  dim3 grid((std::min(a.R, a.rm.T) + rb - 1) / rb, a.Hkv, nseq);
   if (a.hd == 64) launch_k((k_attn_prefill<T, 64>), grid, dim3(64 * PF_NW), 0, s, a);
   else if (a.hd == 128) launch_k((k_attn_prefill<T, 128>), grid, dim3(64 * PF_NW), 0, s, a);
   else return -1;
@@ -782,7 +783,7 @@ int launch_attn_decode(int dtype, const AttnArgs& a, Stream s) {
 }
 int launch_attn_prefill(int dtype, const AttnArgs& a, Stream s) {
   if (a.H % a.Hkv != 0 || a.S % 64 != 0 || a.rm.mode != ROWS_PREFILL || a.rm.T < 1 || a.R < 1) return -1;
-  return dtype == 1 ? prefill_t<bf16>(a, s) : prefill_t<float>(a, s);
+  return dtype == 1 ? launch_attn_prompt(a, s) : prefill_t<float>(a, s);
 }
 
 }  // namespace ham

@@ -36,7 +36,7 @@ struct PrefillArgs {
 struct GatherArgs {
   const int* ids; int R; const void* E; int d, V; float* x; int ldx;
   const float* rows;                // if set: copy fp32 rows [R][d] from here instead of gathering E rows
-  int* err; long long g0; int T;    // err of row r's sequence, (g0 + r) / T: set (bit 2) if its id is out of range
+  int* err; int b0, s0, T;          // err of row r's sequence, b0 + (s0 + r) / T: set (bit 2) if its id is out of range
 };
 
 struct GenArgs {

@@ -408,7 +408,7 @@ __global__ __launch_bounds__(256) void k_gather_rows(GatherArgs a) {
   }
   int t = a.ids[r];
   if (t < 0 || t >= a.V) {  // caller-provided id out of range: flag it, read row 0
-    if (threadIdx.x == 0) atomicOr(a.err + (a.g0 + r) / a.T, 2);
+    if (threadIdx.x == 0) atomicOr(a.err + a.b0 + (a.s0 + r) / a.T, 2);
     t = 0;
   }
   const T* E = (const T*)a.E;

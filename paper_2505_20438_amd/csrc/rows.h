@@ -13,10 +13,11 @@ __device__ __forceinline__ RowInfo row_info(const RowMap& rm, int r) {
   RowInfo ri;
   switch (rm.mode) {
     case ROWS_PREFILL: {  // one slot per input row, causal; position = slot unless given
-      const long long g = rm.g0 + r;
-      ri.b = (int)(g / rm.T);
-      ri.slot = (int)(g - (long long)ri.b * rm.T);
-      ri.pos = rm.pos ? rm.pos[g] : ri.slot;
+      // T and a launch's rows are below 2^24 + 2^11, and g0 = b0 * T + s0
+      const unsigned t = (unsigned)(rm.s0 + r), q = t / (unsigned)rm.T;
+      ri.b = rm.b0 + (int)q;
+      ri.slot = (int)(t - q * (unsigned)rm.T);
+      ri.pos = rm.pos ? rm.pos[(size_t)ri.b * rm.T + ri.slot] : ri.slot;
       ri.n_valid = ri.slot + 1;
       ri.enabled = 1;
       break;
