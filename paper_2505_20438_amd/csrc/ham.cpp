@@ -62,7 +62,7 @@ constexpr int MAX_ATTN_SPLIT = 64;
 constexpr int LOCAL_SLOTS = 64;
 
 size_t attn_part_bytes(int R, int H, int Hk, int hd);
-int attn_splits_for(int dtype, int R, int Hk, int kv_max);
+int attn_splits_for(int dtype, int R, int Hk, int hd, int kv_max);
 
 struct Layout {
   // dims
@@ -655,7 +655,7 @@ int run_layer(ham_model* m, int j, int R, const RowMap& rm, float*& x, bool pref
   ra.K = Kc; ra.VT = VTc; ra.sb = sb; ra.sh = sh; ra.S = S; ra.H = y.H; ra.Hkv = y.Hk; ra.hd = y.hd;
   ra.cos_t = m->W<float>(y.cos_t); ra.sin_t = m->W<float>(y.sin_t); ra.max_pos = y.max_pos; ra.rm = rm;
   ra.gate = gate; ra.gate_n = gate_n;
-  launch_rope_append(dt, ra, s);
+  if (launch_rope_append(dt, ra, s)) return fail(HAM_EINVAL, "rope shape");
   if (kv_only) return HAM_OK;  // only this layer's K and V of these rows are read later
 
   AttnArgs aa{};
@@ -759,16 +759,16 @@ int decode_tail(ham_model* m, Pending& pend, float* ctx_last, float* xres, int* 
   return HAM_OK;
 }
 
-// slot splits across workgroups: none while every wave of a workgroup gets at
-// most a few key blocks; otherwise enough to give about 4096 waves in total
-int attn_splits_for(int dtype, int R, int Hk, int kv_max) {
-  const int kb = dtype == HAM_BF16 ? 32 : 16;
+// Slot splits of the filled-cache attention: none while the keys of a (row, kv head) are under 128 KB (one workgroup
+// then reads them about as fast as the extra combine launch, 4 us, takes), else about one workgroup per CU, two key
+// blocks or more each.  Measured, bf16, 8 kv heads, us unsplit / split: head dim 128, 1 row: 512 slots 10.4 / 9.1, 2,048
+// slots 27.9 / 10.2, 32K slots 433 / 29; 8 rows x 4,096 60.5 / 27.9; 16 rows x 512 12.5 / 12.9; 32 rows 86 / 93 (256
+// workgroups already).  Twice as many workgroups: 4 rows x 32K 86 -> 94, 8 rows x 2,048 18.4 -> 20.0.
+int attn_splits_for(int dtype, int R, int Hk, int hd, int kv_max) {
+  const int es = dtype == HAM_BF16 ? 2 : 4, kb = dtype == HAM_BF16 ? 32 : 16;
+  if ((long long)kv_max * hd * es < 128 * 1024) return 1;
   const int blocks = (kv_max + kb - 1) / kb;
-  if (blocks <= 8 * 8) return 1;  // 8 waves x at most 8 blocks each
-  const int wgs = R * Hk;
-  int want = (4096 / 8 + wgs - 1) / wgs;
-  const int most = std::max(1, blocks / (8 * 2));  // at least 2 blocks per wave
-  return std::max(1, std::min(std::min(want, most), MAX_ATTN_SPLIT));
+  return std::max(1, std::min(std::min(256 / (R * Hk), (blocks + 1) / 2), MAX_ATTN_SPLIT));
 }
 
 size_t attn_part_bytes(int R, int H, int Hk, int hd) {
@@ -999,7 +999,7 @@ int prefill_common(ham_model* m, int32_t batch, int32_t T, const int32_t* d_prom
   AttnArgs aa{};
   aa.q = m->WS<char>(y.emb_o); aa.ldq = y.HD; aa.K = m->st + y.Kc + l * y.kv_layer; aa.VT = m->st + y.VTc + l * y.kv_layer;
   aa.sb = sb; aa.sh = sh; aa.S = y.S; aa.H = y.H; aa.Hkv = y.Hk; aa.hd = y.hd; aa.R = batch;
-  aa.nsplit = attn_splits_for(dt, batch, y.Hk, T); aa.o = m->WS<char>(y.ao); aa.ldo = y.HD;
+  aa.nsplit = attn_splits_for(dt, batch, y.Hk, y.hd, T); aa.o = m->WS<char>(y.ao); aa.ldo = y.HD;
   aa.part = m->WS<float>(y.apart); aa.rm.mode = ROWS_DECODE; aa.rm.st = m->sp;
   if (launch_attn_decode(dt, aa, s) != 0) return fail(HAM_EINVAL, "attention shape");
   Pending pend;
@@ -1310,7 +1310,7 @@ int ham_op_decode_attention(int32_t dtype, int32_t rows, int32_t H, int32_t Hk, 
   AttnArgs aa{};
   aa.q = d_q; aa.ldq = H * hd; aa.K = d_k; aa.VT = d_vt; aa.sb = (long long)Hk * S * hd;
   aa.sh = (long long)S * hd; aa.S = S; aa.H = H; aa.Hkv = Hk; aa.hd = hd; aa.R = rows;
-  aa.nsplit = attn_splits_for(dtype, rows, Hk, std::max(kv_max, 1));
+  aa.nsplit = attn_splits_for(dtype, rows, Hk, hd, std::max(kv_max, 1));
   aa.o = d_out; aa.ldo = H * hd; aa.part = (float*)d_ws;
   aa.rm.mode = ROWS_DECODE; aa.rm.st = sp;
   if (launch_attn_decode(dtype, aa, (hipStream_t)stream)) return fail(HAM_EINVAL, "attention shape");
