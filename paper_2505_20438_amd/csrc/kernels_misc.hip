@@ -256,15 +256,44 @@ int launch_rmsnorm(int dtype, const NormArgs& a, Stream s) {
 // ---------------------------------------------------------------- RoPE + KV append
 // Rotate-half RoPE of q and k at the row's position; q -> q buffer, k -> K cache slot, v -> its column of the slot's
 // V tile.  Bound by memory: the fp32 projections (or their split-K partials) in, 4 bytes per q value and the cache type
-// out.  The first `nqk` blocks take q and k, four value pairs a thread with 16-byte loads; the others take v of one kv
-// head and 32 rows each through LDS, so that a store covers neighbouring slots of a tile row (one head's row per
-// 64-thread block, 4-byte loads and a 2-byte store per cache line before).  2,048 rows of the 8B shape: 33 us before,
-// 21 us now.
-constexpr int ROPE_VR = 32;  // rows of a v block
+// out.  The first `nqk` blocks take q and k, four value pairs a thread with 16-byte loads; the others take 64 columns of
+// v of one kv head and 32 rows each through LDS, so that a store covers neighbouring slots of a tile row (one head's row
+// per 64-thread block, 4-byte loads and a 2-byte store per cache line before).  2,048 rows of the 8B shape: 33 us
+// before, 21 us now.  Few rows are bound by the chain of loads over the partials, so these come in batches of eight,
+// for both items of a thread: 20 rows of the 8B shape with 11 partials 5.5 us, 13.1 with one
+// partial at a time.
+constexpr int ROPE_VR = 32, ROPE_VC = 64;  // rows and columns of a v block
+
+// v[i] = the partials at p[i] in split order (n >= 1 of them, `stride` floats apart)
+template <int N>
+__device__ __forceinline__ void sum_partials(f4 (&v)[N], const float* const (&p)[N], int n, size_t stride) {
+  if (n == 1) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = *reinterpret_cast<const f4*>(p[i]);
+    return;
+  }
+  constexpr int NB = 8;
+  for (int s0 = 0; s0 < n; s0 += NB) {
+    f4 t[NB][N];
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+      if (s0 + q < n) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[q][i] = *reinterpret_cast<const f4*>(p[i] + (size_t)(s0 + q) * stride);
+      }
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+      if (s0 + q < n) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = s0 + q == 0 ? t[q][i] : v[i] + t[q][i];
+      }
+  }
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void k_rope_append(RopeArgs a, int nqk) {
   if (!any_flag(a.gate, a.gate_n)) return;
-  __shared__ float sv[ROPE_VR][128 + 1];
+  __shared__ float sv[ROPE_VR][ROPE_VC + 1];
   const int ns = a.part ? a.nsplit : 1;
   const float* src = a.part ? a.part : a.qkv;
   const size_t sstride = (size_t)a.R * a.ldqkv;
@@ -285,12 +314,9 @@ __global__ __launch_bounds__(256) void k_rope_append(RopeArgs a, int nqk) {
     const f4 c = *reinterpret_cast<const f4*>(a.cos_t + (size_t)ri.pos * half + i);
     const f4 sn = *reinterpret_cast<const f4*>(a.sin_t + (size_t)ri.pos * half + i);
     const float* p = src + (size_t)r * a.ldqkv + hh * a.hd + i;
-    f4 x1 = *reinterpret_cast<const f4*>(p), x2 = *reinterpret_cast<const f4*>(p + half);
-    for (int s = 1; s < ns; ++s) {  // the split-K partials of the projection in split order
-      x1 += *reinterpret_cast<const f4*>(p + s * sstride);
-      x2 += *reinterpret_cast<const f4*>(p + s * sstride + half);
-    }
-    const f4 y1 = x1 * c - x2 * sn, y2 = x2 * c + x1 * sn;
+    f4 x[2];
+    sum_partials(x, {p, p + half}, ns, sstride);
+    const f4 y1 = x[0] * c - x[1] * sn, y2 = x[1] * c + x[0] * sn;
     if (hh < a.H) {
       put4<T>(a.q, r, a.ldq, hh * a.hd + i, y1);
       put4<T>(a.q, r, a.ldq, hh * a.hd + i + half, y2);
@@ -301,15 +327,22 @@ __global__ __launch_bounds__(256) void k_rope_append(RopeArgs a, int nqk) {
     }
     return;
   }
-  const int vb = blockIdx.x - nqk, kvh = vb % a.Hkv, r0 = vb / a.Hkv * ROPE_VR, cpr = a.hd / 4;
-  for (int t = threadIdx.x; t < ROPE_VR * cpr; t += 256) {
-    const int rr = t / cpr, i = t % cpr * 4, r = r0 + rr;
-    if (r < a.R) {
-      const float* p = src + (size_t)r * a.ldqkv + (size_t)(a.H + a.Hkv + kvh) * a.hd + i;
-      f4 v = *reinterpret_cast<const f4*>(p);
-      for (int s = 1; s < ns; ++s) v += *reinterpret_cast<const f4*>(p + s * sstride);
+  const int ndt = (a.hd + ROPE_VC - 1) / ROPE_VC;
+  const int vb = blockIdx.x - nqk, d0 = vb % ndt * ROPE_VC, kvh = vb / ndt % a.Hkv, r0 = vb / (ndt * a.Hkv) * ROPE_VR;
+  static_assert(ROPE_VR * ROPE_VC / 4 == 2 * 256, "two items a thread");
+  {
+    constexpr int CPR = ROPE_VC / 4;
+    const int i = threadIdx.x % CPR * 4, rr = threadIdx.x / CPR;
+    if (r0 + rr < a.R && d0 + i < a.hd) {
+      const float* p = src + (size_t)(r0 + rr) * a.ldqkv + (size_t)(a.H + a.Hkv + kvh) * a.hd + d0 + i;
+      const bool two = r0 + rr + 16 < a.R;
+      f4 v[2];
+      sum_partials(v, {p, two ? p + (size_t)16 * a.ldqkv : p}, ns, sstride);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sv[rr][i + e] = v[e];
+      for (int e = 0; e < 4; ++e) {
+        sv[rr][i + e] = v[0][e];
+        sv[rr + 16][i + e] = v[1][e];
+      }
     }
   }
   __syncthreads();
@@ -318,14 +351,18 @@ __global__ __launch_bounds__(256) void k_rope_append(RopeArgs a, int nqk) {
   const RowInfo ri = row_info(a.rm, r);
   if (!ok(ri) || !ri.enabled) return;  // reported by the row's q and k
   T* v = (T*)a.VT + ri.b * a.sb + kvh * a.sh;
-  for (int d = threadIdx.x / ROPE_VR; d < a.hd; d += 256 / ROPE_VR) v[vt_offset(d, ri.slot, a.hd)] = from_f<T>(sv[rr][d]);
+#pragma unroll
+  for (int u = 0; u < ROPE_VC * ROPE_VR / 256; ++u) {
+    const int i = threadIdx.x / ROPE_VR + u * (256 / ROPE_VR);
+    if (d0 + i < a.hd) v[vt_offset(d0 + i, ri.slot, a.hd)] = from_f<T>(sv[rr][i]);
+  }
 }
 
 int launch_rope_append(int dtype, const RopeArgs& a, Stream s) {
   if (a.R <= 0) return 0;
   if (a.hd % 8 != 0 || a.hd > 128 || a.ldqkv % 4 != 0) return -1;
   const int nqk = (int)(((long long)a.R * (a.H + a.Hkv) * (a.hd / 8) + 255) / 256);
-  const dim3 grid(nqk + (a.R + ROPE_VR - 1) / ROPE_VR * a.Hkv);
+  const dim3 grid(nqk + (a.R + ROPE_VR - 1) / ROPE_VR * a.Hkv * ((a.hd + ROPE_VC - 1) / ROPE_VC));
   if (dtype == 1) launch_k((k_rope_append<bf16>), grid, dim3(256), 0, s, a, nqk);
   else launch_k((k_rope_append<float>), grid, dim3(256), 0, s, a, nqk);
   return 0;
