@@ -113,6 +113,11 @@ constexpr uint32_t BUF_OOB = 0xFFFFFFF0u;
 __device__ __forceinline__ BufRsrc buf_rsrc(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
 }
+// an offset past every descriptor of less than 2 GB, also when a small offset is added to it
+constexpr uint32_t BUF_FAR = 0x80000000u;
+__device__ __forceinline__ u4 buf_u4(BufRsrc r, uint32_t off) {
+  return __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
 __device__ __forceinline__ f4 buf_f4(BufRsrc r, uint32_t off) {
   return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
 }

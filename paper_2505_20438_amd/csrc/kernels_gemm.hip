@@ -3,7 +3,7 @@
 // Weights are stored fragment-tiled (device_common.h): every wave load of a
 // weight fragment is one contiguous 1 KB block, and the waves of a workgroup
 // take interleaved k-fragments so that together they read one contiguous
-// window.  Four matrix-core kernels share one set of fused epilogues:
+// window.  The matrix-core kernels share one set of fused epilogues:
 //  * k_gemm_skinny (M <= 8 rows: decode, micro steps, LM head; up to 64 for
 //    the embedder's output epilogues).  HBM-bound
 //    weight streaming with non-temporal loads; four waves split the k-range of
@@ -20,6 +20,8 @@
 //    would produce X disappears from the launch sequence.
 //  * k_gemm_wide (8 < M <= 64, in fp32 256: batched decode, micro context rows): eight
 //    waves own eight column tiles and share X chunks through LDS.
+//  * k_gemm_rows (8 < M <= 32 in bf16, q/k/v, gate/up and the embedder): eight waves
+//    share eight column tiles and split their k-range, X straight from memory.
 //  * larger M (prompt chunks): kernels_prompt.hip in bf16; in fp32 k_gemm_pf
 //    (M > 256, LDS ring) and k_gemm_big (128x128 LDS-staged tiles, double
 //    buffered, 2x2 waves of 64x64).
@@ -898,6 +900,174 @@ __global__ __launch_bounds__(64 * WIDE_NW) void k_gemm_wide(GemmArgs a) {
   if (tile_ok) skinny_epilogue<T, MT, TN, EPI>(a, acc, ntile, split, nsplit, n0);
 }
 
+// ------------------------------------------------------------------------ rows
+// The q/k/v, gate/up and embedder projections of 9..32 rows in bf16 (decode batches).  Bound by streaming the weights, and that by how it meets the memory: a
+// workgroup of eight waves owns eight neighbouring 16-column tiles and one k-range, and wave w takes the k-fragments
+// w, w + 8, ... of all eight, so the waves read one window of 8 KB of every tile (waves that own a tile each read
+// twice as many windows, of 4 KB).  A fragment of X is used by one wave of the workgroup only and comes straight into
+// its registers, for eight tiles of products: no LDS, no barrier in the loop.  It runs one workgroup per CU, and so takes the
+// projections that one round of workgroups covers: 32 rows of the 8B shape, k_gemm_wide against this: q/k/v 17.9 / 14.6
+// us, gate/up 47.7 and 5.0 for the reduction of its splits / 45.0 (5.2 TB/s, unsplit); 20 rows 19.2 / 13.9 and 44.8 +
+// 4.8 / 43.3; 16 rows of the 1B shape 8.1 / 7.9 and 18.5 / 16.2.  Not the LM head (four rounds, each with its own fill
+// and reduction: 190 / 214), the o-projection and the down projection (17.9 / 18.4).
+// Every load is a range-checked buffer load, also past the k-range: a load under a condition makes the compiler wait,
+// before each use of an older fragment, as if the newer one had not been issued, that is for all of them.
+// NX: X is the RMSNorm of fp32 rows whose sums of squares the norm's first phase left in 256-column chunks (XS_NORMW):
+// scaled by the row's 1/rms and the gain and split into the operand planes in registers.
+constexpr int ROWS_NW = 8, ROWS_TN = 8, ROWS_MAX_M = 32;
+
+template <int MT, bool NX>
+struct RowsFrag {
+  u4 w[ROWS_TN];
+  u4 x0[MT], x1[MT];  // hi and lo plane, or (NX) eight fp32 values
+  u4 g0, g1;          // NX: their gains
+};
+
+template <typename T, int MT, int EPI, int TAG, bool NX>
+__global__ __launch_bounds__(64 * ROWS_NW) void k_gemm_rows(GemmArgs a) {
+  if (!any_flag(a.gate, a.gate_n)) return;
+  static_assert(Act<T>::SPLIT, "bf16");
+  constexpr int KB = Frag<T>::KB, NW = ROWS_NW, TN = ROWS_TN;
+  __shared__ float red[NW][TN][MT * 4][64];
+  __shared__ float rinv_s[16 * MT];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, g = lane >> 4;
+  const int split = blockIdx.y, nsplit = gridDim.y;
+  const int nfr = a.K / KB, tile0 = blockIdx.x * TN;
+  const int c0 = (int)((long)split * nfr / nsplit), c1 = (int)((long)(split + 1) * nfr / nsplit);
+  const int nk = c1 - c0, cnt = nk > w ? (nk - w + NW - 1) / NW : 0;
+  // tiles past N and rows past M lie past the descriptors' ends: zeros
+  const BufRsrc rw = buf_rsrc((const char*)a.W + (size_t)tile0 * nfr * 1024,
+                              (uint32_t)min(TN, a.N / 16 - tile0) * (uint32_t)nfr * 1024u);
+  const BufRsrc rx = NX ? buf_rsrc(a.xs.x, (uint32_t)a.M * a.xs.ldx * 4u) : buf_rsrc(a.X, (uint32_t)a.M * a.ldx * 4u);
+  const BufRsrc rg = buf_rsrc(NX ? (const void*)a.xs.g : a.X, NX ? (uint32_t)a.K * 4u : 0u);
+  uint32_t xo[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+    xo[i] = NX ? ((uint32_t)(16 * i + r16) * a.xs.ldx + g * 8u) * 4u : (uint32_t)(16 * i + r16) * a.ldx * 4u + g * 16u;
+  auto load = [&](RowsFrag<MT, NX>& b, int i) {
+    const int f = c0 + w + NW * i;
+    const bool in = f < c1;
+    if constexpr (NX) {
+      const uint32_t go = in ? (uint32_t)(f * KB + g * 8) * 4u : BUF_FAR;
+      b.g0 = buf_u4(rg, go);
+      b.g1 = buf_u4(rg, go + 16u);
+    }
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const uint32_t o = in ? xo[t] + (uint32_t)f * (NX ? KB * 4u : KB * 2u) : BUF_FAR;
+      b.x0[t] = buf_u4(rx, o);
+      b.x1[t] = buf_u4(rx, o + (NX ? 16u : (uint32_t)a.ldx * 2u));
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+      b.w[j] = buf_u4_stream(rw, (in ? (uint32_t)(j * nfr + f) * 1024u : BUF_FAR) + lane * 16u);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  float inv[MT];
+  f4 acc[MT][TN];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    inv[t] = 1.f;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[t][j] = f4{0.f, 0.f, 0.f, 0.f};
+  }
+  auto mma = [&](const RowsFrag<MT, NX>& b) {
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      u4 h = b.x0[t], l = b.x1[t];
+      if constexpr (NX) {
+        float v[8], r[8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[e] = __uint_as_float(b.x0[t][e]) * inv[t] * __uint_as_float(b.g0[e]);
+          v[e + 4] = __uint_as_float(b.x1[t][e]) * inv[t] * __uint_as_float(b.g1[e]);
+        }
+        h = pack_frag_bf16(v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) r[e] = v[e] - bf2f((bf16)((e & 1) ? h[e >> 1] >> 16 : h[e >> 1] & 0xFFFFu));
+        l = pack_frag_bf16(r);
+      }
+#pragma unroll
+      for (int j = 0; j < TN; ++j) mma_act<T>(acc[t][j], h, l, b.w[j]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // each row's 1/rms from the chunk sums, in chunk order; its first loads go ahead of the weights
+  constexpr int SB = 16;
+  float sq[SB];
+  const BufRsrc rs = buf_rsrc(NX ? (const void*)a.xs.ssw : a.X, NX ? (uint32_t)a.M * a.xs.nchw * 4u : 0u);
+  auto sload = [&](int q0) {
+#pragma unroll
+    for (int q = 0; q < SB; ++q)
+      sq[q] = buf_f1(rs, tid < a.M && q0 + q < a.xs.nchw ? (uint32_t)(tid * a.xs.nchw + q0 + q) * 4u : BUF_FAR);
+  };
+  if constexpr (NX) sload(0);
+  // two fragments in registers, three where they fit: one feeds the matrix cores, the others are in flight
+  constexpr bool THREE = MT == 1 && !NX;
+  RowsFrag<MT, NX> b0, b1, b2;
+  load(b0, 0);
+  if constexpr (THREE) load(b1, 1);
+  if constexpr (NX) {
+    if (tid < 16 * MT) {
+      float t = 0.f;
+#pragma unroll
+      for (int q = 0; q < SB; ++q) t += sq[q];
+      for (int q0 = SB; q0 < a.xs.nchw; q0 += SB) {
+        sload(q0);
+#pragma unroll
+        for (int q = 0; q < SB; ++q) t += sq[q];
+      }
+      rinv_s[tid] = tid < a.M ? 1.0f / sqrtf(t / (float)a.K + a.xs.eps) : 0.f;
+    }
+    lds_barrier();
+#pragma unroll
+    for (int t = 0; t < MT; ++t) inv[t] = rinv_s[16 * t + r16];
+  }
+  if constexpr (!THREE) {
+    for (int i = 0; i < cnt; i += 2) {
+      load(b1, i + 1);
+      mma(b0);
+      if (i + 1 >= cnt) break;
+      load(b0, i + 2);
+      mma(b1);
+    }
+  } else {
+    for (int i = 0; i < cnt; i += 3) {
+      load(b2, i + 2);
+      mma(b0);
+      if (i + 1 >= cnt) break;
+      load(b0, i + 3);
+      mma(b1);
+      if (i + 2 >= cnt) break;
+      load(b1, i + 4);
+      mma(b2);
+    }
+  }
+  // the waves' k-slices, added in wave order; wave w finishes tile w
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[w][j][4 * t + r][lane] = acc[t][j][r];
+  lds_barrier();
+  static_assert(NW == TN, "a wave per tile");
+  const int n0 = (tile0 + w) * 16;
+  if (n0 >= a.N) return;
+  f4 out[MT][1];
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float v = red[0][w][4 * t + r][lane];
+#pragma unroll
+      for (int q = 1; q < NW; ++q) v += red[q][w][4 * t + r][lane];
+      out[t][0][r] = v;
+    }
+  skinny_epilogue<T, MT, 1, EPI>(a, out, tile0 + w, split, nsplit, n0);
+}
+
 // Final argmax of one row over all column tiles (fixed total order: larger value,
 // then lower index), then the decision and stop test of that sequence, then
 // (a sequence still running) the input rows of the next micro step, so no
@@ -1428,6 +1598,31 @@ static int gemm_wide(GemmArgs a, int max_split, int tag, Stream s, int* nsplit_o
     return 0;
   }
 
+// as many k-splits as one workgroup per CU takes, with at least two fragments per wave (SwiGLU then finishes in
+// k_split_reduce)
+template <int EPI, bool NX = false>
+static int gemm_rows(GemmArgs a, int max_split, int tag, Stream s, int* nsplit_out) {
+  const int groups = (a.N + 16 * ROWS_TN - 1) / (16 * ROWS_TN), nfr = a.K / Frag<bf16>::KB;
+  int nsplit = 1;
+  if (max_split > 1 || EPI == EPI_SWIGLU)
+    nsplit = std::min(std::min(GPU_CUS / groups, nfr / (2 * ROWS_NW)),
+                      EPI == EPI_SWIGLU ? MAX_WIDE_SWIGLU_SPLIT : max_split);
+  nsplit = std::max(1, std::min(nsplit, PART_ROWS / a.M));
+  a.nsplit = nsplit;
+  *nsplit_out = EPI == EPI_SWIGLU ? 1 : nsplit;
+  const dim3 grid(groups, nsplit), block(64 * ROWS_NW);
+  if (a.M <= 16) {
+    if (!tag) launch_k((k_gemm_rows<bf16, 1, EPI, 0, NX>), grid, block, 0, s, a);
+    else launch_k((k_gemm_rows<bf16, 1, EPI, 1, NX>), grid, block, 0, s, a);
+  } else {
+    if (!tag) launch_k((k_gemm_rows<bf16, 2, EPI, 0, NX>), grid, block, 0, s, a);
+    else launch_k((k_gemm_rows<bf16, 2, EPI, 1, NX>), grid, block, 0, s, a);
+  }
+  if (EPI == EPI_SWIGLU && nsplit > 1)
+    launch_k((k_split_reduce<bf16, EPI_SWIGLU>), dim3((a.N / 2 + 255) / 256, a.M), dim3(256), 0, s, a);
+  return 0;
+}
+
 template <typename T, int EPI>
 static int gemm_t(const GemmArgs& a0, int max_split, int tag, Stream s, int* nsplit_out, bool dry = false) {
   GemmArgs a = a0;
@@ -1440,6 +1635,8 @@ static int gemm_t(const GemmArgs& a0, int max_split, int tag, Stream s, int* nsp
       if (a.M > 8 && a.M <= WIDE_MAX_M<T> && a.K % WIDE_KC == 0 && a.xs.x && a.xs.g && a.xs.ssw &&
           a.xs.nchw == (a.K + 255) / 256) {
         if (dry) return 0;
+        if constexpr (std::is_same<T, bf16>::value)
+          if (a.M <= ROWS_MAX_M) return gemm_rows<EPI, true>(a, max_split, tag, s, nsplit_out);
         return gemm_wide<T, EPI, true>(a, max_split, tag, s, nsplit_out);
       }
     }
@@ -1462,8 +1659,11 @@ static int gemm_t(const GemmArgs& a0, int max_split, int tag, Stream s, int* nsp
     // the row scale is applied by the skinny kernel of one 16-row tile only
     if (a.rs.ss && (a.M > NORM_OUT_MAX_ROWS || a.rs.n < 1 || a.rs.n > NORM_OUT_MAX_TILES)) return -1;
   }
-  if (a.M > 8 && a.M <= WIDE_MAX_M<T> && a.K % WIDE_KC == 0 && EPI != EPI_XMASK && EPI != EPI_OP)
+  if (a.M > 8 && a.M <= WIDE_MAX_M<T> && a.K % WIDE_KC == 0 && EPI != EPI_XMASK && EPI != EPI_OP) {
+    if constexpr (std::is_same<T, bf16>::value && (EPI == EPI_F32 || EPI == EPI_SWIGLU))
+      if (a.M <= ROWS_MAX_M) return gemm_rows<EPI>(a, max_split, tag, s, nsplit_out);
     return gemm_wide<T, EPI>(a, max_split, tag, s, nsplit_out);
+  }
   if (a.M > 64) {
     if constexpr (EPI == EPI_ARGMAX) {
       return -1;

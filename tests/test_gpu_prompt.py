@@ -67,3 +67,11 @@ def test_prompt_rows_past_a_tile(dtype, prompt):
     (dataclasses.replace(EDGES, dtype=F32), 3, 77, [0, 1, 2]), (dataclasses.replace(EDGES, dtype=F32), 3, 1100, [1])])
 def test_prompts_share_chunks(shape, batch, prompt, rows):
     _check(shape, batch, prompt, rows)
+
+
+# 9 to 33 rows: the kernel of small row counts (a wave per 16 columns of 128, row tiles of 16, k split over its waves) as
+# a prompt's plain rows and as the normed rows of the first micro step (4 rows a sequence), at widths that end inside its
+# 128 columns and give its waves unequal shares of the fragments (20 of d = 640); q/k/v 768, gate/up 2112 columns.
+@pytest.mark.parametrize("batch,prompt", [(1, 9), (4, 4), (3, 6), (8, 4), (11, 3)])
+def test_small_row_counts(batch, prompt):
+    _check(dataclasses.replace(EDGES, d_model=640), batch, prompt, sorted({0, batch // 2, batch - 1}))
