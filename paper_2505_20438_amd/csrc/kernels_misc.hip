@@ -16,6 +16,11 @@ __device__ __forceinline__ void store4(float* p, f4 v) { *reinterpret_cast<f4*>(
 __device__ __forceinline__ void store4(bf16* p, f4 v) {
   *reinterpret_cast<uint2*>(p) = uint2{f2bf2(v[0], v[1]), f2bf2(v[2], v[3])};
 }
+__device__ __forceinline__ f4 load4(const float* p) { return *reinterpret_cast<const f4*>(p); }
+__device__ __forceinline__ f4 load4(const bf16* p) {
+  const uint2 v = *reinterpret_cast<const uint2*>(p);
+  return f4{bf2f((bf16)(v.x & 0xFFFFu)), bf2f((bf16)(v.x >> 16)), bf2f((bf16)(v.y & 0xFFFFu)), bf2f((bf16)(v.y >> 16))};
+}
 template <typename T> __device__ __forceinline__ void put4(void* base, size_t row, int W, int i, f4 v);
 template <> __device__ __forceinline__ void put4<float>(void* base, size_t row, int W, int i, f4 v) {
   store4((float*)base + row * W + i, v);
@@ -260,8 +265,8 @@ int launch_rmsnorm(int dtype, const NormArgs& a, Stream s) {
 // v of one kv head and 32 rows each through LDS, so that a store covers neighbouring slots of a tile row (one head's row
 // per 64-thread block, 4-byte loads and a 2-byte store per cache line before).  2,048 rows of the 8B shape: 33 us
 // before, 21 us now.  Few rows are bound by the chain of loads over the partials, so these come in batches of eight,
-// for both items of a thread: 20 rows of the 8B shape with 11 partials 5.5 us, 13.1 with one
-// partial at a time.
+// for both items of a thread: 20 rows of the 8B shape with 11 partials 5.5 us, 13.1 with one partial at
+// a time.
 constexpr int ROPE_VR = 32, ROPE_VC = 64;  // rows and columns of a v block
 
 // v[i] = the partials at p[i] in split order (n >= 1 of them, `stride` floats apart)
@@ -372,8 +377,12 @@ int launch_rope_append(int dtype, const RopeArgs& a, Stream s) {
 // For each sequence: consume the previous group (fuse it or bypass), advance the
 // position by the group size (the fused input sits at its last token's position,
 // Sec. 3.2), take the next KV slot, and open a new group.
+// Bound by latency: one workgroup per sequence, four columns a thread, so that d = 4096 is one round trip (two 2-byte
+// loads a thread and row in a loop before: 20.6 us at 4 rows of the 8B shape, 5.1 now; 32 rows 25.0,
+// 5.8; one row of the 1B shape 8.0, 4.3).
+constexpr int MACRO_THREADS = 1024;
 template <typename T>
-__global__ __launch_bounds__(256) void k_macro_begin(MacroArgs a) {
+__global__ __launch_bounds__(MACRO_THREADS) void k_macro_begin(MacroArgs a) {
   __shared__ int sh[7];  // n, on, new position, tokens 0..3
   const int b = blockIdx.x, tid = threadIdx.x;
   const SeqPtrs& st = a.st;
@@ -388,6 +397,17 @@ __global__ __launch_bounds__(256) void k_macro_begin(MacroArgs a) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) sh[3 + j] = j < n ? t[j] : 0;
   }
+  // the last thread keeps the books; what it needs beyond the above loads meanwhile
+  const bool books = tid == MACRO_THREADS - 1;
+  int kv_len = 0, forced = a.G, teacher[4] = {0, 0, 0, 0};
+  if (books) {
+    kv_len = st.kv_len[b];
+    if (a.forced_in) forced = a.forced_in[b];
+    if (a.teacher_in) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) teacher[j] = a.teacher_in[b * 4 + j];
+    }
+  }
   __syncthreads();
   const int n = sh[0], on = sh[1], p = sh[2];
   const int spos = on ? min(max(p, 0), a.max_pos - 1) : -1;
@@ -397,63 +417,51 @@ __global__ __launch_bounds__(256) void k_macro_begin(MacroArgs a) {
   // RoPE factors of this step's base input (read by every layer's attention step),
   // loaded together with the embedding rows
   if (spos >= 0)
-    for (int i = tid; i < half; i += 256) {
+    for (int i = tid; i < half; i += MACRO_THREADS) {
       a.rope_cs[(size_t)b * a.hd + i] = a.cos_t[(size_t)spos * half + i];
       a.rope_cs[(size_t)b * a.hd + half + i] = a.sin_t[(size_t)spos * half + i];
     }
   if (on && n == 1) {  // bypass: the single token's embedding is the base input
-    constexpr int U = 8;
     const T* er = E + (size_t)sh[3] * d;
-    for (int i0 = tid; i0 < d; i0 += 256 * U) {
-      float v[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) v[u] = i0 + 256 * u < d ? to_f<T>(er[i0 + 256 * u]) : 0.f;
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (i0 + 256 * u < d) a.x[(size_t)b * a.ldx + i0 + 256 * u] = v[u];
-    }
+    for (int i = tid * 4; i < d; i += MACRO_THREADS * 4) store4(a.x + (size_t)b * a.ldx + i, load4(er + i));
   } else if (on && n > 1) {
     // e_j = E[t_j] + P[j]; query = mean_j e_j; rows of the embedder's projection GEMM
-    constexpr int U = 2;
-    for (int i0 = tid; i0 < d; i0 += 256 * U) {
-      float ev[U][4], pv[U][4];
+    for (int i = tid * 4; i < d; i += MACRO_THREADS * 4) {
+      f4 ev[4], pv[4];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int i = i0 + 256 * u;
-          const bool ok = i < d && j < n;
-          ev[u][j] = ok ? to_f<T>(E[(size_t)sh[3 + j] * d + i]) : 0.f;
-          pv[u][j] = ok ? to_f<T>(P[(size_t)j * d + i]) : 0.f;
+      for (int j = 0; j < 4; ++j) {
+        ev[j] = f4{0.f, 0.f, 0.f, 0.f};
+        pv[j] = f4{0.f, 0.f, 0.f, 0.f};
+        if (j < n) {
+          ev[j] = load4(E + (size_t)sh[3 + j] * d + i);
+          pv[j] = load4(P + (size_t)j * d + i);
         }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = i0 + 256 * u;
-        if (i >= d) continue;
-        float sum = 0.f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float e = j < n ? ev[u][j] + pv[u][j] : 0.f;
-          sum += e;
-          Act<T>::put(a.emb_in, (size_t)b * 5 + 1 + j, d, i, e);
-        }
-        Act<T>::put(a.emb_in, (size_t)b * 5, d, i, sum / (float)n);
       }
+      f4 sum = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f4 e = ev[j] + pv[j];
+        sum += e;
+        put4<T>(a.emb_in, (size_t)b * 5 + 1 + j, d, i, e);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum[e] /= (float)n;
+      put4<T>(a.emb_in, (size_t)b * 5, d, i, sum);
     }
   }
-  if (tid == 0) {
+  if (books) {
     st.step_on[b] = on;
     st.fused[b] = (on && n > 1) ? n : 0;
     if (on) {
       st.pos_last[b] = p;
       st.cur_pos[b] = p;
-      st.cur_slot[b] = st.kv_len[b];
-      st.kv_len[b] += 1;
+      st.cur_slot[b] = kv_len;
+      st.kv_len[b] = kv_len + 1;
       if (p < 0 || p >= a.max_pos) atomicOr(st.err + b, 1);
     }
-    st.forced[b] = a.forced_in ? a.forced_in[b] : a.G;
+    st.forced[b] = forced;
     for (int j = 0; j < 4; ++j) {
-      st.teacher[b * 4 + j] = a.teacher_in ? a.teacher_in[b * 4 + j] : 0;
+      st.teacher[b * 4 + j] = teacher[j];
       a.out_tokens[b * 4 + j] = -1;
     }
     a.out_lens[b] = 0;
@@ -616,7 +624,7 @@ __global__ void k_fill_f32(float* p, long long n, float v) {
   } while (0)
 
 void launch_macro_begin(int dtype, const MacroArgs& a, Stream s) {
-  HAM_T_LAUNCH(dtype, k_macro_begin, dim3(a.B), dim3(256), s, a);
+  HAM_T_LAUNCH(dtype, k_macro_begin, dim3(a.B), dim3(MACRO_THREADS), s, a);
 }
 void launch_embed_attn(int dtype, const EmbedAttnArgs& a, Stream s) {
   HAM_T_LAUNCH(dtype, k_embed_attn, dim3(a.B, a.H), dim3(64), s, a);
