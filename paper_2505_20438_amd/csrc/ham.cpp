@@ -17,6 +17,7 @@
 
 #include "ham_internal.h"
 #include "kernels_misc.h"
+#include "launch_rules.h"
 
 using namespace ham;
 
@@ -58,11 +59,9 @@ uint64_t sm64(uint64_t s, uint64_t i) {
 }
 
 constexpr int MAX_GEMM_SPLIT = 16;
-constexpr int MAX_ATTN_SPLIT = 64;
 constexpr int LOCAL_SLOTS = 64;
 
 size_t attn_part_bytes(int R, int H, int Hk, int hd);
-int attn_splits_for(int dtype, int R, int Hk, int hd, int kv_max);
 
 struct Layout {
   // dims
@@ -759,18 +758,6 @@ int decode_tail(ham_model* m, Pending& pend, float* ctx_last, float* xres, int* 
   return HAM_OK;
 }
 
-// Slot splits of the filled-cache attention: none while the keys of a (row, kv head) are under 128 KB (one workgroup
-// then reads them about as fast as the extra combine launch, 4 us, takes), else about one workgroup per CU, two key
-// blocks or more each.  Measured, bf16, 8 kv heads, us unsplit / split: head dim 128, 1 row: 512 slots 10.4 / 9.1, 2,048
-// slots 27.9 / 10.2, 32K slots 433 / 29; 8 rows x 4,096 60.5 / 27.9; 16 rows x 512 12.5 / 12.9; 32 rows 86 / 93 (256
-// workgroups already).  Twice as many workgroups: 4 rows x 32K 86 -> 94, 8 rows x 2,048 18.4 -> 20.0.
-int attn_splits_for(int dtype, int R, int Hk, int hd, int kv_max) {
-  const int es = dtype == HAM_BF16 ? 2 : 4, kb = dtype == HAM_BF16 ? 32 : 16;
-  if ((long long)kv_max * hd * es < 128 * 1024) return 1;
-  const int blocks = (kv_max + kb - 1) / kb;
-  return std::max(1, std::min(std::min(256 / (R * Hk), (blocks + 1) / 2), MAX_ATTN_SPLIT));
-}
-
 size_t attn_part_bytes(int R, int H, int Hk, int hd) {
   return (size_t)R * Hk * MAX_ATTN_SPLIT * (H / Hk) * (hd + 2) * 4;
 }
@@ -999,7 +986,7 @@ int prefill_common(ham_model* m, int32_t batch, int32_t T, const int32_t* d_prom
   AttnArgs aa{};
   aa.q = m->WS<char>(y.emb_o); aa.ldq = y.HD; aa.K = m->st + y.Kc + l * y.kv_layer; aa.VT = m->st + y.VTc + l * y.kv_layer;
   aa.sb = sb; aa.sh = sh; aa.S = y.S; aa.H = y.H; aa.Hkv = y.Hk; aa.hd = y.hd; aa.R = batch;
-  aa.nsplit = attn_splits_for(dt, batch, y.Hk, y.hd, T); aa.o = m->WS<char>(y.ao); aa.ldo = y.HD;
+  aa.nsplit = attn_decode_splits(dt, batch, y.Hk, y.hd, T); aa.o = m->WS<char>(y.ao); aa.ldo = y.HD;
   aa.part = m->WS<float>(y.apart); aa.rm.mode = ROWS_DECODE; aa.rm.st = m->sp;
   if (launch_attn_decode(dt, aa, s) != 0) return fail(HAM_EINVAL, "attention shape");
   Pending pend;
@@ -1310,7 +1297,7 @@ int ham_op_decode_attention(int32_t dtype, int32_t rows, int32_t H, int32_t Hk, 
   AttnArgs aa{};
   aa.q = d_q; aa.ldq = H * hd; aa.K = d_k; aa.VT = d_vt; aa.sb = (long long)Hk * S * hd;
   aa.sh = (long long)S * hd; aa.S = S; aa.H = H; aa.Hkv = Hk; aa.hd = hd; aa.R = rows;
-  aa.nsplit = attn_splits_for(dtype, rows, Hk, hd, std::max(kv_max, 1));
+  aa.nsplit = attn_decode_splits(dtype, rows, Hk, hd, std::max(kv_max, 1));
   aa.o = d_out; aa.ldo = H * hd; aa.part = (float*)d_ws;
   aa.rm.mode = ROWS_DECODE; aa.rm.st = sp;
   if (launch_attn_decode(dtype, aa, (hipStream_t)stream)) return fail(HAM_EINVAL, "attention shape");

@@ -1,0 +1,42 @@
+// Launch rules that depend on sizes alone, without a GPU or a HIP header, so that they can be checked by themselves.
+#pragma once
+#include <algorithm>
+
+namespace ham {
+
+constexpr int MAX_ATTN_SPLIT = 64;
+
+// Slot splits of the filled-cache attention for R rows of Hk kv heads of which the longest has kv_max slots: none while
+// the keys of a (row, kv head) are under 128 KB (one workgroup then reads them about as fast as the extra combine
+// launch, 4 us, takes), else the count with the least estimated time for rows of equal length, two key blocks or more
+// each.  One workgroup runs per CU, so R * Hk * splits workgroups take ceil(... / 256) rounds; a workgroup needs 3.4 us
+// and, per 32 slots of head dim 128 in bf16 (16 KB), 0.42 us alone and 0.59 with all 256 at work.  That takes splits whose
+// last round is full.  8 kv heads of 128 in bf16, us at 256 / (R * Hk) splits rounded down and at the splits here: 12 rows x
+// 4,096 slots 44.3 / 42.8, 17 x 8,192 131 / 105, 20 x 4,096 72 / 64, 24 x 32K 540 / 476, 40 x 4,096 150 / 124, 48 x 8,192
+// 287 / 257; the same where 256 workgroups come out even (1 x 2,048 10.4, 8 x 4,096 29, 32 x 4,096 87, 4 x 32K 89).
+// A row's slots are shared by its own splits alone, so a long row among short ones is a serial chain.  From 2 MB of keys
+// (8,192 such slots: 111 us unsplit) a row gets at least two rounds' share, up to 8 splits.  One row of 32K slots and the
+// rest of 500: 8 rows 126 -> 75 us, 20 rows 444 -> 75, 40 rows 445 -> 129; where all are long this costs 8 x 32K 169 ->
+// 177, 16 x 8,192 89 -> 97 and 32 x 8,192 165 -> 174.
+inline int attn_decode_splits(int dtype, int R, int Hk, int hd, int kv_max) {
+  const int es = dtype == 1 ? 2 : 4, kb = dtype == 1 ? 32 : 16;
+  const long long keys = (long long)kv_max * hd * es, pairs = (long long)R * Hk;
+  if (keys < 128 * 1024) return 1;
+  const int blocks = (kv_max + kb - 1) / kb, most = std::max(1, std::min((blocks + 1) / 2, MAX_ATTN_SPLIT));
+  int least = 1;
+  if (keys >= 2 * 1024 * 1024) least = (int)std::min({(512 + pairs - 1) / pairs, 8ll, (long long)most});
+  int best = least;
+  double best_t = 1e30;
+  for (int s = least; s <= most; ++s) {
+    const double rounds = (double)((pairs * s + 255) / 256), last = (double)(pairs * s) / 256 - (rounds - 1);
+    const double units = (double)((blocks + s - 1) / s) * hd / 128;  // of 16 KB
+    const double t = rounds * 3.4 + units * (0.59 * (rounds - 1) + 0.42 + 0.17 * last) + (s > 1 ? 4 : 0);
+    if (t < best_t) {
+      best_t = t;
+      best = s;
+    }
+  }
+  return best;
+}
+
+}  // namespace ham

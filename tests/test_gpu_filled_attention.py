@@ -17,7 +17,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype,H,Hk,hd,lens", [
     (BF16, 32, 8, 128, [511]), (BF16, 32, 8, 128, [512]), (BF16, 32, 8, 128, [4097, 1]),
     (BF16, 32, 8, 64, [1023] * 2), (BF16, 32, 8, 64, [1024, 0, 33]), (BF16, 9, 3, 64, [2000, 40, 1999, 65]),
-    (BF16, 8, 8, 128, [700] * 40), (BF16, 4, 2, 128, [9000]), (F32, 32, 8, 64, [511, 513, 700]), (F32, 6, 2, 128, [3001])])
+    (BF16, 8, 8, 128, [700] * 40), (BF16, 4, 2, 128, [9000]), (F32, 32, 8, 64, [511, 513, 700]), (F32, 6, 2, 128, [3001]),
+    (BF16, 32, 8, 128, [4096] + [700] * 16), (BF16, 8, 2, 128, [500, 33, 0] * 5 + [8192]), (F32, 4, 2, 128, [4100, 16, 15])])
 def test_filled_attention_splits(dtype, H, Hk, hd, lens):
     import torch
     assert torch.cuda.is_available(), "GPU tests need a GPU"

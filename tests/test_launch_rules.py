@@ -1,0 +1,41 @@
+"""The launch rules that pick a kernel's split or form from sizes alone (``csrc/launch_rules.h``), on the CPU."""
+import pytest
+
+from synth.configs import BF16, F32
+from tests.rules_util import rules
+
+CUS = 256
+
+
+@pytest.mark.parametrize("dtype,hd,kv", [(BF16, 128, 4096), (BF16, 128, 8192), (BF16, 128, 32768), (BF16, 64, 16384), (F32, 128, 4096)])
+def test_filled_attention_keeps_the_gpu_busy(dtype, hd, kv):
+    # one workgroup runs per CU: their number fills at least 7/10 of the rounds that it takes, at every row count
+    for hk in (2, 8):
+        for rows in range(1, 65):
+            wgs = rows * hk * rules().splits(dtype, rows, hk, hd, kv)
+            assert wgs >= 0.7 * CUS * -(-wgs // CUS) or wgs == rows * hk * 64, (hk, rows, wgs)
+
+
+@pytest.mark.parametrize("dtype,hd,kv", [(BF16, 128, 8192), (BF16, 128, 32768), (BF16, 64, 16384), (F32, 128, 4096), (F32, 64, 9000)])
+def test_long_rows_are_shared(dtype, hd, kv):
+    # a row's slots are shared by its own splits alone, and the batch may be ragged: from 2 MB of keys a row has up to 8
+    # splits while two rounds of workgroups hold them
+    for hk in (1, 2, 3, 8, 32):
+        for rows in range(1, 65):
+            assert rules().splits(dtype, rows, hk, hd, kv) >= min(8, -(-2 * CUS // (rows * hk))), (hk, rows)
+
+
+def test_filled_attention_split_limits():
+    for dtype, hd, kb, es in ((BF16, 64, 32, 2), (BF16, 128, 32, 2), (F32, 64, 16, 4), (F32, 128, 16, 4)):
+        for rows in (1, 2, 7, 40, 64, 1000):
+            for hk in (1, 8, 64):
+                for kv in (1, 31, 128 * 1024 // (hd * es) - 1, 128 * 1024 // (hd * es), 1000, 5000, 1 << 24):
+                    s = rules().splits(dtype, rows, hk, hd, kv)
+                    assert 1 <= s <= max(1, min(64, (-(-kv // kb) + 1) // 2))   # two key blocks or more each
+                    assert s == 1 or kv * hd * es >= 128 * 1024
+
+
+@pytest.mark.parametrize("rows,kv,splits", [(1, 512, 8), (2, 1999, 16), (1, 2048, 32), (8, 2048, 4), (8, 4096, 4), (32, 4096, 1),
+                                            (64, 4096, 1), (1, 32768, 32), (4, 32768, 8)])
+def test_filled_attention_splits_where_one_round_is_full(rows, kv, splits):
+    assert rules().splits(BF16, rows, 8, 128, kv) == splits
