@@ -20,7 +20,7 @@
 //    would produce X disappears from the launch sequence.
 //  * k_gemm_wide (8 < M <= 64, in fp32 256: batched decode, micro context rows): eight
 //    waves own eight column tiles and share X chunks through LDS.
-//  * k_gemm_rows (8 < M <= 32 in bf16, q/k/v, gate/up and the embedder): eight waves
+//  * k_gemm_rows (8 < M <= 32 in bf16, q/k/v, gate/up and the embedder, see gemm_rows_takes): eight waves
 //    share eight column tiles and split their k-range, X straight from memory.
 //  * larger M (prompt chunks): kernels_prompt.hip in bf16; in fp32 k_gemm_pf
 //    (M > 256, LDS ring) and k_gemm_big (128x128 LDS-staged tiles, double
@@ -35,6 +35,7 @@
 #include "device_common.h"
 #include "gemm_epilogue.h"
 #include "ham_internal.h"
+#include "launch_rules.h"
 
 namespace ham {
 
@@ -906,7 +907,7 @@ __global__ __launch_bounds__(64 * WIDE_NW) void k_gemm_wide(GemmArgs a) {
 // w, w + 8, ... of all eight, so the waves read one window of 8 KB of every tile (waves that own a tile each read
 // twice as many windows, of 4 KB).  A fragment of X is used by one wave of the workgroup only and comes straight into
 // its registers, for eight tiles of products: no LDS, no barrier in the loop.  It runs one workgroup per CU, and so takes the
-// projections that one round of workgroups covers: 32 rows of the 8B shape, k_gemm_wide against this: q/k/v 17.9 / 14.6
+// projections whose rounds of workgroups are well filled (gemm_rows_takes): 32 rows of the 8B shape, k_gemm_wide against this: q/k/v 17.9 / 14.6
 // us, gate/up 47.7 and 5.0 for the reduction of its splits / 45.0 (5.2 TB/s, unsplit); 20 rows 19.2 / 13.9 and 44.8 +
 // 4.8 / 43.3; 16 rows of the 1B shape 8.1 / 7.9 and 18.5 / 16.2.  Not the LM head (four rounds, each with its own fill
 // and reduction: 190 / 214), the o-projection and the down projection (17.9 / 18.4).
@@ -914,7 +915,7 @@ __global__ __launch_bounds__(64 * WIDE_NW) void k_gemm_wide(GemmArgs a) {
 // before each use of an older fragment, as if the newer one had not been issued, that is for all of them.
 // NX: X is the RMSNorm of fp32 rows whose sums of squares the norm's first phase left in 256-column chunks (XS_NORMW):
 // scaled by the row's 1/rms and the gain and split into the operand planes in registers.
-constexpr int ROWS_NW = 8, ROWS_TN = 8, ROWS_MAX_M = 32;
+constexpr int ROWS_NW = 8, ROWS_TN = 8;
 
 template <int MT, bool NX>
 struct RowsFrag {
@@ -1636,7 +1637,7 @@ static int gemm_t(const GemmArgs& a0, int max_split, int tag, Stream s, int* nsp
           a.xs.nchw == (a.K + 255) / 256) {
         if (dry) return 0;
         if constexpr (std::is_same<T, bf16>::value)
-          if (a.M <= ROWS_MAX_M) return gemm_rows<EPI, true>(a, max_split, tag, s, nsplit_out);
+          if (gemm_rows_takes(a.M, a.N)) return gemm_rows<EPI, true>(a, max_split, tag, s, nsplit_out);
         return gemm_wide<T, EPI, true>(a, max_split, tag, s, nsplit_out);
       }
     }
@@ -1661,7 +1662,7 @@ static int gemm_t(const GemmArgs& a0, int max_split, int tag, Stream s, int* nsp
   }
   if (a.M > 8 && a.M <= WIDE_MAX_M<T> && a.K % WIDE_KC == 0 && EPI != EPI_XMASK && EPI != EPI_OP) {
     if constexpr (std::is_same<T, bf16>::value && (EPI == EPI_F32 || EPI == EPI_SWIGLU))
-      if (a.M <= ROWS_MAX_M) return gemm_rows<EPI>(a, max_split, tag, s, nsplit_out);
+      if (gemm_rows_takes(a.M, a.N)) return gemm_rows<EPI>(a, max_split, tag, s, nsplit_out);
     return gemm_wide<T, EPI>(a, max_split, tag, s, nsplit_out);
   }
   if (a.M > 64) {

@@ -39,4 +39,19 @@ inline int attn_decode_splits(int dtype, int R, int Hk, int hd, int kv_max) {
   return best;
 }
 
+// Whether k_gemm_rows takes a bf16 projection of M rows and N columns (k range a multiple of 128).  It runs one workgroup
+// of 128 columns per CU, so its time grows by rounds of 256 where k_gemm_wide's grows with the columns: a second round
+// has to be an eighth full at up to 16 rows and a quarter full at 32, and at 32 rows a fourth does not pay.  Gate/up, us,
+// k_gemm_wide with the reduction of its splits / k_gemm_rows: k 4,096, 32 rows: 224 groups of columns 51 / 45, 260 73 / 79,
+// 288 76 / 80, 320 85 / 81, 520 131 / 125, 768 170 / 145, 780 173 / 174; 16 rows: 260 71 / 69, 288 76 / 71, 780 166 / 153;
+// k 8,192, 32 rows: 260 130 / 150, 288 139 / 153, 320 152 / 154, 448 201 / 175, 780 316 / 334; 16 rows: 260 126 / 134,
+// 288 140 / 134.
+constexpr int ROWS_MAX_M = 32;
+inline bool gemm_rows_takes(int M, int N) {
+  if (M <= 8 || M > ROWS_MAX_M) return false;
+  const int groups = (N + 127) / 128;
+  if (groups > 256 && groups < 512) return groups >= (M <= 16 ? 288 : 320);
+  return M <= 16 || groups <= 768;
+}
+
 }  // namespace ham

@@ -10,12 +10,13 @@ SHIM = """#include "launch_rules.h"
 extern "C" int splits(int dtype, int R, int Hk, int hd, int kv_max) {
   return ham::attn_decode_splits(dtype, R, Hk, hd, kv_max);
 }
+extern "C" int rows_takes(int M, int N) { return ham::gemm_rows_takes(M, N); }
 """
 
 
 @functools.lru_cache(None)
 def rules():
-    """Library with ``splits(dtype, rows, n_kv_heads, head_dim, kv_max)``."""
+    """Library with ``splits(dtype, rows, n_kv_heads, head_dim, kv_max)`` and ``rows_takes(M, N)``."""
     with tempfile.TemporaryDirectory() as d:
         src, out = os.path.join(d, "rules.cpp"), os.path.join(d, "rules.so")
         with open(src, "w") as f:

@@ -75,3 +75,10 @@ def test_prompts_share_chunks(shape, batch, prompt, rows):
 @pytest.mark.parametrize("batch,prompt", [(1, 9), (4, 4), (3, 6), (8, 4), (11, 3)])
 def test_small_row_counts(batch, prompt):
     _check(dataclasses.replace(EDGES, d_model=640), batch, prompt, sorted({0, batch // 2, batch - 1}))
+
+
+# the same row counts at a width whose second round of 128-column groups is nearly empty (gate/up 33,280 columns: 260
+# groups), where the batched kernel takes them
+@pytest.mark.parametrize("batch,prompt", [(3, 4), (7, 4)])
+def test_small_row_counts_wide(batch, prompt):
+    _check(dataclasses.replace(EDGES, n_layers=2, d_model=256, ffn_dim=16640), batch, prompt, [0, batch - 1])

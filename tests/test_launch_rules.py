@@ -39,3 +39,11 @@ def test_filled_attention_split_limits():
                                             (64, 4096, 1), (1, 32768, 32), (4, 32768, 8)])
 def test_filled_attention_splits_where_one_round_is_full(rows, kv, splits):
     assert rules().splits(BF16, rows, 8, 128, kv) == splits
+
+
+# q/k/v 6,144 columns, the embedder 12,288, gate/up 28,672 and (wider models) beyond one round of 256 x 128 columns
+@pytest.mark.parametrize("rows,cols,takes", [(9, 6144, 1), (32, 12288, 1), (32, 28672, 1), (32, 32768, 1), (8, 28672, 0), (33, 28672, 0),
+                                             (32, 32800, 0), (32, 33280, 0), (16, 33280, 0), (16, 36864, 1), (17, 36864, 0), (32, 40960, 1),
+                                             (32, 57344, 1), (32, 65536, 1), (32, 99840, 0), (16, 99840, 1)])
+def test_row_kernel_takes_well_filled_rounds(rows, cols, takes):
+    assert rules().rows_takes(rows, cols) == takes
