@@ -22,11 +22,10 @@
 // masks and the zeroing of values past the end run only in blocks that reach past the wave's first row.  8B shape,
 // 2,048 rows at slots 30,720..32,767: 2,270 -> 1,798 us, 1,185 TFLOP/s executed (16x16x32 products, about 25 vector
 // instructions per score and two exchanges per block before); rows 0..2,047: 155 -> 99 us.
-#include <algorithm>
-
 #include "device_common.h"
 #include "gemm_epilogue.h"
 #include "ham_internal.h"
+#include "launch_rules.h"
 #include "rows.h"
 
 namespace ham {
@@ -37,7 +36,7 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 // in whole contiguous 1 KB pieces.  K keeps its rows (16-byte chunk c of slot r at chunk c ^ (r mod row's chunks)),
 // V its tile rows (chunk c of row d at c ^ (d / 4 % 4)): the swizzles spread a wave's operand reads over all banks.
 template <int HD> struct PA {
-  static constexpr int NW = 8, KB = 32, NBL = 2, NS = 4;
+  static constexpr int NW = PROMPT_ATTN_WAVES, KB = 32, NBL = 2, NS = 4;
   static constexpr int KC = HD / 8, KU = KB * KC;       // 16-byte chunks per K row, per block
   static constexpr int VU = HD * 4, BU = KU + VU;       // chunks of a V tile, of a block
   static constexpr int PIECES = NBL * BU / 64, LPW = PIECES / NW;  // 1 KB pieces per stage, per wave
@@ -254,7 +253,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_prompt(AttnArgs a) {
         for (int e = 0; e < 16; ++e) rec[(2 + d * 16 + e) * 64] = o[d][e];
     }
     __syncthreads();
-    if (kg == 1) return;
+    if (kg == 1 || !rows_ok) return;  // waves without rows (two of eight at three q-heads a kv head) have no record
     {
       const float m1 = rec[0], mnew = fmaxf(mrun, m1);
       const float a0 = mrun == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mrun - mnew);
@@ -286,25 +285,15 @@ __global__ __launch_bounds__(512, 2) void k_attn_prompt(AttnArgs a) {
     }
 }
 
-// The keys form while the rows form would give no more than every other CU a workgroup (one sequence, rows / keys form:
-// 512 rows of the 1B shape 20.2 / 17.0 us, 1,024 rows 35.5 / 28.7 and of the 8B shape 54.7 / 46.1; above that the rows
-// form wins: 2,048 rows 68.9 / 96.0 and 99.4 / 142.5).
-constexpr int PA_KEYS_MAX_WGS = 128;
-
 int launch_attn_prompt(const AttnArgs& a, Stream s) {
-  const int grp = a.H / a.Hkv;
-  if (a.H % a.Hkv != 0 || grp > 4 || a.S % 64 != 0 || a.rm.mode != ROWS_PREFILL || a.rm.T < 1 || a.R < 1) return -1;
-  // sequences that have rows in the launch, and the row blocks of the longest share
-  const int nseq = (a.rm.s0 + a.R - 1) / a.rm.T + 1, most = std::min(a.R, a.rm.T);
-  const int nt = (most + 31) / 32, nrg = PA<64>::NW / grp, half = nrg / 2;  // row tiles, those of a workgroup
-  const int rows_wgs = ((nt + 1) / 2 + half - 1) / half;
-  const bool keys = (long)rows_wgs * a.Hkv * nseq <= PA_KEYS_MAX_WGS;
-  const dim3 grid(keys ? (nt + half - 1) / half : rows_wgs, a.Hkv, nseq);
+  if (a.H % a.Hkv != 0 || a.H / a.Hkv > 4 || a.S % 64 != 0 || a.rm.mode != ROWS_PREFILL || a.rm.T < 1 || a.R < 1) return -1;
+  const PromptAttnGrid pg = prompt_attn_grid(a.R, a.rm.s0, a.rm.T, a.H, a.Hkv);
+  const dim3 grid(pg.blocks, a.Hkv, pg.seqs);
   if (a.hd == 64) {
-    if (keys) launch_k((k_attn_prompt<64, true>), grid, dim3(512), 0, s, a);
+    if (pg.keys) launch_k((k_attn_prompt<64, true>), grid, dim3(512), 0, s, a);
     else launch_k((k_attn_prompt<64, false>), grid, dim3(512), 0, s, a);
   } else if (a.hd == 128) {
-    if (keys) launch_k((k_attn_prompt<128, true>), grid, dim3(512), 0, s, a);
+    if (pg.keys) launch_k((k_attn_prompt<128, true>), grid, dim3(512), 0, s, a);
     else launch_k((k_attn_prompt<128, false>), grid, dim3(512), 0, s, a);
   } else {
     return -1;

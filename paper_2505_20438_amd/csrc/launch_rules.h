@@ -54,4 +54,22 @@ inline bool gemm_rows_takes(int M, int N) {
   return M <= 16 || groups <= 768;
 }
 
+// Grid of the bf16 prompt attention (kernels_attn_prompt.hip): `blocks` x kv heads x `seqs` workgroups of eight waves, for
+// R rows from input s0 of a sequence on, through sequences of T inputs.  Tiles of 32 rows; `blocks` covers the longest share
+// of a sequence.  The keys form while the rows form would give no more than every other CU a workgroup (one sequence,
+// rows / keys form: 512 rows of the 1B shape 20.2 / 17.0 us, 1,024 rows 35.5 / 28.7 and of the 8B shape 54.7 / 46.1; above
+// that the rows form wins: 2,048 rows 68.9 / 96.0 and 99.4 / 142.5).
+constexpr int PROMPT_ATTN_WAVES = 8, PROMPT_ATTN_KEYS_MAX_WGS = 128;
+struct PromptAttnGrid {
+  int blocks, seqs;
+  bool keys;
+};
+inline PromptAttnGrid prompt_attn_grid(int R, int s0, int T, int H, int Hkv) {
+  const int seqs = (s0 + R - 1) / T + 1, tiles = (std::min(R, T) + 31) / 32;
+  const int half = PROMPT_ATTN_WAVES / (H / Hkv) / 2;  // row tiles of a workgroup: 2 * half (rows form) or half
+  const int rows_blocks = ((tiles + 1) / 2 + half - 1) / half;
+  const bool keys = (long)rows_blocks * Hkv * seqs <= PROMPT_ATTN_KEYS_MAX_WGS;
+  return PromptAttnGrid{keys ? (tiles + half - 1) / half : rows_blocks, seqs, keys};
+}
+
 }  // namespace ham

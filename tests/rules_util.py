@@ -10,13 +10,16 @@ SHIM = """#include "launch_rules.h"
 extern "C" int splits(int dtype, int R, int Hk, int hd, int kv_max) {
   return ham::attn_decode_splits(dtype, R, Hk, hd, kv_max);
 }
+extern "C" int prompt_keys(int R, int s0, int T, int H, int Hk) { return ham::prompt_attn_grid(R, s0, T, H, Hk).keys; }
+extern "C" int prompt_blocks(int R, int s0, int T, int H, int Hk) { return ham::prompt_attn_grid(R, s0, T, H, Hk).blocks; }
 extern "C" int rows_takes(int M, int N) { return ham::gemm_rows_takes(M, N); }
 """
 
 
 @functools.lru_cache(None)
 def rules():
-    """Library with ``splits(dtype, rows, n_kv_heads, head_dim, kv_max)`` and ``rows_takes(M, N)``."""
+    """Library with ``splits(dtype, rows, n_kv_heads, head_dim, kv_max)``, ``rows_takes(M, N)`` and ``prompt_keys`` /
+    ``prompt_blocks(rows, first input, inputs of a sequence, n_heads, n_kv_heads)``."""
     with tempfile.TemporaryDirectory() as d:
         src, out = os.path.join(d, "rules.cpp"), os.path.join(d, "rules.so")
         with open(src, "w") as f:

@@ -47,3 +47,24 @@ def test_filled_attention_splits_where_one_round_is_full(rows, kv, splits):
                                              (32, 57344, 1), (32, 65536, 1), (32, 99840, 0), (16, 99840, 1)])
 def test_row_kernel_takes_well_filled_rounds(rows, cols, takes):
     assert rules().rows_takes(rows, cols) == takes
+
+
+@pytest.mark.parametrize("grp", [1, 2, 3, 4])
+def test_prompt_attention_blocks_cover_every_tile(grp):
+    # the tiles of 32 rows that the workgroups of a sequence take, by the kernel's own mapping, are each taken once
+    for rows, s0, T in ((1, 0, 1), (31, 0, 31), (33, 0, 33), (77, 0, 77), (300, 0, 300), (1232, 0, 77), (1664, 500, 1100), (2048, 0, 4096)):
+        for hk in (1, 2, 8, 32):
+            keys, blocks = rules().prompt_keys(rows, s0, T, grp * hk, hk), rules().prompt_blocks(rows, s0, T, grp * hk, hk)
+            for z in range((s0 + rows - 1) // T + 1):
+                lo, hi = max(z * T - s0, 0), min(z * T - s0 + T, rows)
+                nt, groups = -(-(hi - lo) // 32), 8 // grp
+                taken = []
+                for x in range(blocks):
+                    if keys:
+                        n = groups // 2
+                        taken += [t for t in range(x * n, x * n + n) if t < nt]
+                    else:
+                        half = groups // 2
+                        for t in range(x * half, x * half + half):
+                            taken += ([t] if 2 * t < nt else []) + ([nt - 1 - t] if 2 * t < nt - 1 else [])
+                assert sorted(taken) == list(range(nt)), (rows, s0, T, hk, keys, z)
