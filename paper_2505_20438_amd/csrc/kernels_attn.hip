@@ -570,9 +570,9 @@ constexpr int PF_NW = 8, PF_NBL = 2, PF_RT = 2;
 #define HAM_PFA_NS 4
 #endif
 constexpr int PFA_NS = HAM_PFA_NS;  // stages of key blocks in the LDS ring (PFA_NS - 1 in flight)
-template <typename T, int HD>
+template <int HD>
 struct PrefillBlock {  // 1 KB fragments of one key block in LDS: K (tile, fragment), then V (d-tile)
-  static constexpr int KB = Frag<T>::KB, EPL = Frag<T>::EPL, NF = HD / KB, ND = HD / 16, TT = KB / 16;
+  static constexpr int KB = Frag<float>::KB, EPL = Frag<float>::EPL, NF = HD / KB, ND = HD / 16, TT = KB / 16;
   static constexpr int KF = TT * NF, VF = ND, BF = KF + VF;
   static constexpr int KU = KF * 64, BU = BF * 64;
 };
@@ -584,7 +584,7 @@ __device__ __forceinline__ void pfa_wait_vm_lgkm0() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
 }
 
-// Prefill: causal attention of a prompt chunk (rows of mode PREFILL, of one
+// Prefill, fp32: causal attention of a prompt chunk (rows of mode PREFILL, of one
 // or more sequences).  One workgroup of PF_NW waves per (row chunk of a
 // sequence, kv head): wave w takes q-head kvh*grp + w % grp and PF_RT tiles of 16 rows from
 // row 16*PF_RT*(w / grp) of the chunk, so a chunk is 16*PF_RT*(PF_NW / grp)
@@ -593,9 +593,9 @@ __device__ __forceinline__ void pfa_wait_vm_lgkm0() {
 // stage in a ring of PFA_NS stages, each 1 KB fragment in the lane order the
 // waves read it (K as operand (tile, fragment), V^T as d-tiles), so every
 // operand read is one contiguous 1 KB and no registers hold loads in flight.
-template <typename T, int HD>
+template <int HD>
 __global__ __launch_bounds__(64 * PF_NW) void k_attn_prefill(AttnArgs a) {
-  using PB = PrefillBlock<T, HD>;
+  using PB = PrefillBlock<HD>;
   constexpr int KB = PB::KB, EPL = PB::EPL, NF = PB::NF, ND = PB::ND, TT = PB::TT, KU = PB::KU, BU = PB::BU;
   constexpr int BF = PB::BF, SF = PF_NBL * BF;             // fragments per block, per stage
   constexpr int LPW = SF / PF_NW;                          // wave-loads per stage per wave
@@ -617,22 +617,18 @@ __global__ __launch_bounds__(64 * PF_NW) void k_attn_prefill(AttnArgs a) {
   const int row0 = chunk0 + rg * 16 * PF_RT;
   const bool rows_ok = rg < nrg && row0 < hi;           // waves past the q-heads only load
   const int wave_end = rows_ok ? slot0 + (row0 - chunk0) + min(16 * PF_RT, hi - row0) : 0;
-  const T* Kb = (const T*)a.K + b * a.sb + kvh * a.sh;
-  const T* Vb = (const T*)a.VT + b * a.sb + kvh * a.sh;
+  const float* Kb = (const float*)a.K + b * a.sb + kvh * a.sh;
+  const float* Vb = (const float*)a.VT + b * a.sb + kvh * a.sh;
 
-  u4 qf[PF_RT][NF], ql[PF_RT][NF];
+  u4 qf[PF_RT][NF];
   int limit[PF_RT], tile_end[PF_RT];
-  constexpr int PL = Act<T>::PL;
 #pragma unroll
   for (int t = 0; t < PF_RT; ++t) {
     const int trow = row0 + 16 * t, qrow = trow + r16;
     const bool qok = rows_ok && qrow < hi;
-    const T* qp = (const T*)a.q + (size_t)(qok ? qrow : 0) * a.ldq * PL + (size_t)h * HD + g * EPL;
+    const float* qp = (const float*)a.q + (size_t)(qok ? qrow : 0) * a.ldq + (size_t)h * HD + g * EPL;
 #pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      qf[t][f] = qok ? ld16(qp + f * KB) : zero16();
-      ql[t][f] = (Act<T>::SPLIT && qok) ? ld16(qp + a.ldq + f * KB) : zero16();
-    }
+    for (int f = 0; f < NF; ++f) qf[t][f] = qok ? ld16(qp + f * KB) : zero16();
     // causal: the row at slot s sees slots [0, s]
     limit[t] = qok ? slot0 + (qrow - chunk0) + 1 : 0;
     tile_end[t] = (rows_ok && trow < hi) ? slot0 + (trow - chunk0) + min(16, hi - trow) : 0;
@@ -663,7 +659,7 @@ __global__ __launch_bounds__(64 * PF_NW) void k_attn_prefill(AttnArgs a) {
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
       const int blk = min(stg * PF_NBL + blki[i], nblk - 1);
-      const T* p = isk[i] ? Kb + (size_t)blk * KB * HD + koff[i]
+      const float* p = isk[i] ? Kb + (size_t)blk * KB * HD + koff[i]
                           : Vb + vt_offset(koff[i], blk * KB, HD) + g * (KB / 4);
       __builtin_amdgcn_global_load_lds((const void*)p, (__attribute__((address_space(3))) void*)(slot + dsto[i]),
                                        16, 0, 0);
@@ -695,7 +691,7 @@ __global__ __launch_bounds__(64 * PF_NW) void k_attn_prefill(AttnArgs a) {
     for (int i = 0; i < PF_NBL; ++i) {
       const int blk = st * PF_NBL + i;
       if (blk < nblk && blk * KB < wave_end) {  // blocks past this wave's last row hold nothing it sees
-        KVBlock<T, HD> kv;
+        KVBlock<float, HD> kv;
         const u4* bp = sp + i * BU;
 #pragma unroll
         for (int t = 0; t < TT; ++t)
@@ -706,7 +702,7 @@ __global__ __launch_bounds__(64 * PF_NW) void k_attn_prefill(AttnArgs a) {
 #pragma unroll
         for (int t = 0; t < PF_RT; ++t)
           if (blk * KB < tile_end[t])
-            attn_block<T, HD>(kv, blk * KB, limit[t], wave_end, qf[t], ql[t], scale, mrun[t], lrun[t], o[t]);
+            attn_block<float, HD>(kv, blk * KB, limit[t], wave_end, qf[t], qf[t], scale, mrun[t], lrun[t], o[t]);
       }
     }
   }
@@ -721,7 +717,7 @@ __global__ __launch_bounds__(64 * PF_NW) void k_attn_prefill(AttnArgs a) {
       if (row < hi) {
         const float inv = lj > 0.f ? 1.0f / lj : 0.f;
 #pragma unroll
-        for (int dt = 0; dt < ND; ++dt) Act<T>::put(a.o, row, a.ldo, h * HD + r16 + dt * 16, o[t][dt][i] * inv);
+        for (int dt = 0; dt < ND; ++dt) Act<float>::put(a.o, row, a.ldo, h * HD + r16 + dt * 16, o[t][dt][i] * inv);
       }
     }
 }
@@ -735,16 +731,15 @@ static int decode_t(const AttnArgs& a, Stream s) {
   if (a.nsplit > 1) launch_k((k_attn_combine<T>), dim3(a.R, a.H), dim3(COMBINE_THREADS), 0, s, a);
   return 0;
 }
-template <typename T>
-static int prefill_t(const AttnArgs& a, Stream s) {
+static int prefill_f32(const AttnArgs& a, Stream s) {
   const int grp = a.H / a.Hkv;
   if (grp < 1 || grp > PF_NW) return -1;
   const int rb = 16 * PF_RT * (PF_NW / grp);  // rows per workgroup
   // sequences that have rows in the launch, and the row blocks of the longest share
   const int nseq = (a.rm.s0 + a.R - 1) / a.rm.T + 1;
   dim3 grid((std::min(a.R, a.rm.T) + rb - 1) / rb, a.Hkv, nseq);
-  if (a.hd == 64) launch_k((k_attn_prefill<T, 64>), grid, dim3(64 * PF_NW), 0, s, a);
-  else if (a.hd == 128) launch_k((k_attn_prefill<T, 128>), grid, dim3(64 * PF_NW), 0, s, a);
+  if (a.hd == 64) launch_k((k_attn_prefill<64>), grid, dim3(64 * PF_NW), 0, s, a);
+  else if (a.hd == 128) launch_k((k_attn_prefill<128>), grid, dim3(64 * PF_NW), 0, s, a);
   else return -1;
   return 0;
 }
@@ -783,7 +778,7 @@ int launch_attn_decode(int dtype, const AttnArgs& a, Stream s) {
 }
 int launch_attn_prefill(int dtype, const AttnArgs& a, Stream s) {
   if (a.H % a.Hkv != 0 || a.S % 64 != 0 || a.rm.mode != ROWS_PREFILL || a.rm.T < 1 || a.R < 1) return -1;
-  return dtype == 1 ? launch_attn_prompt(a, s) : prefill_t<float>(a, s);
+  return dtype == 1 ? launch_attn_prompt(a, s) : prefill_f32(a, s);
 }
 
 }  // namespace ham

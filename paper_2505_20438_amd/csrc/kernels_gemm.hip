@@ -1203,24 +1203,24 @@ __global__ __launch_bounds__(256) void k_split_reduce(GemmArgs a) {
   }
 }
 
-// ------------------------------------------------------------------------ big
-template <typename T, int EPI>
+// ------------------------------------------------------------------------ big, fp32
+// 64 < M <= 256 rows of fp32 models whose k range the batched GEMM does not take.
+template <int EPI>
 __global__ __launch_bounds__(256) void k_gemm_big(GemmArgs a) {
   if (!any_flag(a.gate, a.gate_n)) return;
-  constexpr int EPL = Frag<T>::EPL, KB = Frag<T>::KB;
+  constexpr int EPL = Frag<float>::EPL, KB = Frag<float>::KB;
   constexpr int LDR = 5;  // u4 per LDS row: 4 used + 1 pad against bank conflicts
-  constexpr int NA = Act<T>::PL;  // activation planes (hi, lo)
-  __shared__ u4 sA[2][NA][128 * LDR];
+  __shared__ u4 sA[2][128 * LDR];
   __shared__ u4 sB[2][128 * LDR];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int r16 = lane & 15, g = lane >> 4;
   const int wm = w >> 1, wn = w & 1;
   const int m0 = blockIdx.y * 128, n0 = blockIdx.x * 128;
-  const T* W = (const T*)a.W;
-  const T* X = (const T*)a.X;
+  const float* W = (const float*)a.W;
+  const float* X = (const float*)a.X;
   const int lr = tid >> 1, lc = (tid & 1) * 2;
   const bool aok = m0 + lr < a.M;
-  const T* ap = X + (size_t)(aok ? m0 + lr : 0) * a.ldx * NA + lc * EPL;
+  const float* ap = X + (size_t)(aok ? m0 + lr : 0) * a.ldx + lc * EPL;
   // B tile: 8 fragment blocks (16 rows x KB each, 64 u4 in lane order) per stage;
   // thread t copies u4 number 2t and 2t+1 of the 512
   const int nfr = a.K / KB;
@@ -1236,14 +1236,11 @@ __global__ __launch_bounds__(256) void k_gemm_big(GemmArgs a) {
   }
   const int nt0 = n0 / 16;
   const int nst = a.K / KB;
-  u4 ra[NA][2], rb[2];
+  u4 ra[2], rb[2];
   auto gload = [&](int s) {
     const size_t k = (size_t)s * KB;
-#pragma unroll
-    for (int p = 0; p < NA; ++p) {
-      ra[p][0] = aok ? ld16(ap + (size_t)p * a.ldx + k) : zero16();
-      ra[p][1] = aok ? ld16(ap + (size_t)p * a.ldx + k + EPL) : zero16();
-    }
+    ra[0] = aok ? ld16(ap + k) : zero16();
+    ra[1] = aok ? ld16(ap + k + EPL) : zero16();
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const size_t blk = (size_t)(nt0 + (brow[q] >> 4)) * nfr + s;
@@ -1251,11 +1248,8 @@ __global__ __launch_bounds__(256) void k_gemm_big(GemmArgs a) {
     }
   };
   auto sstore = [&](int buf) {
-#pragma unroll
-    for (int p = 0; p < NA; ++p) {
-      sA[buf][p][lr * LDR + lc] = ra[p][0];
-      sA[buf][p][lr * LDR + lc + 1] = ra[p][1];
-    }
+    sA[buf][lr * LDR + lc] = ra[0];
+    sA[buf][lr * LDR + lc + 1] = ra[1];
 #pragma unroll
     for (int q = 0; q < 2; ++q) sB[buf][brow[q] * LDR + bg[q]] = rb[q];
   };
@@ -1270,18 +1264,15 @@ __global__ __launch_bounds__(256) void k_gemm_big(GemmArgs a) {
   for (int s = 0; s < nst; ++s) {
     const int cur = s & 1;
     if (s + 1 < nst) gload(s + 1);
-    u4 af[4], afl[4], bfr[4];
+    u4 af[4], bfr[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      af[i] = sA[cur][0][(wm * 64 + i * 16 + r16) * LDR + g];
-      afl[i] = sA[cur][NA - 1][(wm * 64 + i * 16 + r16) * LDR + g];
-    }
+    for (int i = 0; i < 4; ++i) af[i] = sA[cur][(wm * 64 + i * 16 + r16) * LDR + g];
 #pragma unroll
     for (int j = 0; j < 4; ++j) bfr[j] = sB[cur][(wn * 64 + j * 16 + r16) * LDR + g];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) mma_act<T>(acc[i][j], af[i], afl[i], bfr[j]);
+      for (int j = 0; j < 4; ++j) Frag<float>::mma(acc[i][j], af[i], bfr[j]);
     if (s + 1 < nst) sstore(cur ^ 1);
     __syncthreads();
   }
@@ -1294,7 +1285,7 @@ __global__ __launch_bounds__(256) void k_gemm_big(GemmArgs a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int m = m0 + wm * 64 + i * 16 + 4 * g + r;
-        epi_tile<T, EPI>(a, m, m < a.M, nb, r16, acc[i][j][r]);
+        epi_tile<float, EPI>(a, m, m < a.M, nb, r16, acc[i][j][r]);
       }
     }
 }
@@ -1338,13 +1329,13 @@ __device__ __forceinline__ void pf_tile(int& mt, int& nt) {
   nt = r / gsz;
 }
 
-template <typename T, int EPI, int BM, int BN>
+template <int EPI, int BM, int BN>
 __global__ __launch_bounds__(BM / 64 * 2 * 64) void k_gemm_pf(GemmArgs a) {
   if (!any_flag(a.gate, a.gate_n)) return;
-  constexpr int EPL = Frag<T>::EPL, KB = Frag<T>::KB, PL = Act<T>::PL;
+  constexpr int EPL = Frag<float>::EPL, KB = Frag<float>::KB;
   constexpr int NW = BM / 64 * 2;                // waves: BM/64 rows x 2 columns of 64 x BN/2
   constexpr int WT = BN / 32;                    // 16-column tiles per wave
-  constexpr int NA = (BM / 16) * PL, NBW = BN / 16;  // 1 KB fragments per stage: X (tiles x planes), W (tiles)
+  constexpr int NA = BM / 16, NBW = BN / 16;     // 1 KB fragments per stage: X and W tiles
   constexpr int NL = NA + NBW, LPW = NL / NW;    // wave-loads per stage, per wave
   static_assert(NL % NW == 0, "loads per stage must split evenly over the waves");
   constexpr int FRAG = 64;                       // u4 per fragment
@@ -1356,10 +1347,10 @@ __global__ __launch_bounds__(BM / 64 * 2 * 64) void k_gemm_pf(GemmArgs a) {
   pf_tile(mt, nt);
   const int m0 = mt * BM, n0 = nt * BN;
   const int nfr = a.K / KB, ntile = a.N / 16;
-  const T* W = (const T*)a.W;
-  const T* X = (const T*)a.X;
+  const float* W = (const float*)a.W;
+  const float* X = (const float*)a.X;
   // this wave's loads of a stage: fragment q = w + NW * i (X fragments first)
-  const T* src[LPW];
+  const float* src[LPW];
   int dst[LPW];
   bool isw[LPW];
 #pragma unroll
@@ -1367,9 +1358,8 @@ __global__ __launch_bounds__(BM / 64 * 2 * 64) void k_gemm_pf(GemmArgs a) {
     const int q = w + NW * i;
     dst[i] = q * FRAG;
     if (q < NA) {
-      const int t = q / PL, p = q % PL;
-      const int m = min(m0 + t * 16 + r16, a.M - 1);
-      src[i] = X + ((size_t)m * PL + p) * a.ldx + g * EPL;
+      const int m = min(m0 + q * 16 + r16, a.M - 1);
+      src[i] = X + (size_t)m * a.ldx + g * EPL;
       isw[i] = false;
     } else {
       const int t = min(n0 / 16 + (q - NA), ntile - 1);
@@ -1381,7 +1371,7 @@ __global__ __launch_bounds__(BM / 64 * 2 * 64) void k_gemm_pf(GemmArgs a) {
     u4* slot = ring[s % PF_NS];
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
-      const T* p = src[i] + (size_t)s * (isw[i] ? FRAG * EPL : KB);
+      const float* p = src[i] + (size_t)s * (isw[i] ? FRAG * EPL : KB);
       __builtin_amdgcn_global_load_lds((const void*)p, (__attribute__((address_space(3))) void*)(slot + dst[i]), 16,
                                        0, 0);
     }
@@ -1403,17 +1393,15 @@ __global__ __launch_bounds__(BM / 64 * 2 * 64) void k_gemm_pf(GemmArgs a) {
     // every wave is past stage s - 1: its slot takes stage s + PF_NS - 1
     if (s + PF_NS - 1 < nst) issue(s + PF_NS - 1);
     const u4* slot = ring[s % PF_NS];
-    u4 af[4][PL], bf[WT];
+    u4 af[4], bf[WT];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int p = 0; p < PL; ++p) af[i][p] = slot[((wm * 4 + i) * PL + p) * FRAG + lane];
+    for (int i = 0; i < 4; ++i) af[i] = slot[(wm * 4 + i) * FRAG + lane];
 #pragma unroll
     for (int j = 0; j < WT; ++j) bf[j] = slot[(NA + wn * WT + j) * FRAG + lane];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < WT; ++j) mma_act<T>(acc[i][j], af[i][0], af[i][PL - 1], bf[j]);
+      for (int j = 0; j < WT; ++j) Frag<float>::mma(acc[i][j], af[i], bf[j]);
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -1424,7 +1412,7 @@ __global__ __launch_bounds__(BM / 64 * 2 * 64) void k_gemm_pf(GemmArgs a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int m = m0 + wm * 64 + i * 16 + 4 * g + r;
-        epi_tile<T, EPI>(a, m, m < a.M, nb, r16, acc[i][j][r]);
+        epi_tile<float, EPI>(a, m, m < a.M, nb, r16, acc[i][j][r]);
       }
     }
 }
@@ -1677,15 +1665,15 @@ static int gemm_t(const GemmArgs& a0, int max_split, int tag, Stream s, int* nsp
         // product of 64 x 64) while they still give at least two workgroups per CU
         if ((long)((a.N + 255) / 256) * ((a.M + BM - 1) / BM) >= 512) {
           dim3 grid((a.N + 255) / 256, (a.M + BM - 1) / BM);
-          launch_k((k_gemm_pf<T, EPI, BM, 256>), grid, dim3(BM / 64 * 2 * 64), 0, s, a);
+          launch_k((k_gemm_pf<EPI, BM, 256>), grid, dim3(BM / 64 * 2 * 64), 0, s, a);
         } else {
           dim3 grid((a.N + 127) / 128, (a.M + BM - 1) / BM);
-          launch_k((k_gemm_pf<T, EPI, BM, 128>), grid, dim3(BM / 64 * 2 * 64), 0, s, a);
+          launch_k((k_gemm_pf<EPI, BM, 128>), grid, dim3(BM / 64 * 2 * 64), 0, s, a);
         }
         return 0;
       } else {
         dim3 grid((a.N + 127) / 128, (a.M + 127) / 128);
-        launch_k((k_gemm_big<T, EPI>), grid, dim3(256), 0, s, a);
+        launch_k((k_gemm_big<EPI>), grid, dim3(256), 0, s, a);
         return 0;
       }
     }
