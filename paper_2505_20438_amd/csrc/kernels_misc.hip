@@ -106,7 +106,8 @@ __global__ __launch_bounds__(NORM_THREADS) void k_rmsnorm(NormArgs a) {
 }
 
 // The same for many rows (a prompt chunk, the first micro step of a batch): 256 threads a row, four consecutive values
-// a load and a store, the partials in batches of eight.  Bound by memory; the rows alone fill the GPU.  1,232 rows of
+// a load and a store, the partials in batches of eight; no copy to `hid`, which decisions alone ask for (at most 64
+// rows).  Bound by memory; the rows alone fill the GPU.  1,232 rows of
 // 2,048 with 3 partials: 18 us in the form above (2-byte stores), 10.5 here.
 constexpr int NORM4_MIN_ROWS = 65;
 template <typename T, int NV>
@@ -160,7 +161,6 @@ __global__ __launch_bounds__(256) void k_rmsnorm_rows(NormArgs a) {
     if (i < a.d) {
       const f4 o = v[e] * inv * *reinterpret_cast<const f4*>(a.g + i);
       put4<T>(a.out, r, a.ldo, i, o);
-      if (a.hid) store4(a.hid + (size_t)r * a.ldh + i, o);
     }
   }
 }
@@ -241,7 +241,7 @@ int launch_fold(const NormArgs& a, Stream s) {
 int launch_rmsnorm(int dtype, const NormArgs& a, Stream s) {
   if (a.R <= 0) return 0;
   if (a.d > NORM_THREADS * NORM_MAXV || (a.part && (a.nsplit < 1 || a.nsplit > NORM_MAXS))) return -1;
-  if (a.R >= NORM4_MIN_ROWS && a.d % 4 == 0 && a.ldx % 4 == 0 && a.ldo % 4 == 0 && a.ldctx % 4 == 0 && a.ldh % 4 == 0) {
+  if (a.R >= NORM4_MIN_ROWS && !a.hid && a.d % 4 == 0 && a.ldx % 4 == 0 && a.ldo % 4 == 0 && a.ldctx % 4 == 0) {
     if (dtype == 1) norm_rows_t<bf16>(a, s);
     else norm_rows_t<float>(a, s);
     return 0;
