@@ -109,7 +109,9 @@ typedef struct ham_model ham_model;
 /* Buffer sizes for a configuration (0 if the configuration is invalid).
  * weights: all parameters, norm gains and RoPE tables;
  * state:   the smashed KV cache of every base layer plus per-sequence counters;
- * workspace: activations, split-K partials and counters of one step. */
+ * workspace: activations, split-K partials and counters of one step or of one
+ *   prefill chunk (min(max_batch * max_prompt, 2048) rows, so it grows with
+ *   max_batch also where prompts are short). */
 size_t ham_weights_bytes(const ham_config* cfg);
 size_t ham_state_bytes(const ham_config* cfg);
 size_t ham_workspace_bytes(const ham_config* cfg);
@@ -137,7 +139,10 @@ int ham_init_weights(const ham_config* cfg, uint64_t seed, void* d_weights, size
  *                model's own argmax at each position
  *  d_out_tokens  int32 [batch][4] the emitted group, d_out_lens int32 [batch]
  * Resets all per-sequence state.  HAM_EINVAL on bad sizes, HAM_ECAP if
- * prompt_len > max_prompt or batch > max_batch. */
+ * prompt_len > max_prompt or batch > max_batch.
+ * The prompts of a batch run as one stream of rows, whose total decides chunks,
+ * tile widths and k-splits: the same call repeats itself bit for bit, but a
+ * prompt's results in another batch may differ in rounding. */
 int ham_prefill(ham_model* m, int32_t batch, const int32_t* d_prompt, int32_t prompt_len,
                 const int32_t* h_max_new, const int32_t* d_forced_lens, const int32_t* d_teacher,
                 int32_t* d_out_tokens, int32_t* d_out_lens);
@@ -164,7 +169,9 @@ int ham_macro_step(ham_model* m, const int32_t* d_forced_lens, const int32_t* d_
  * embeddings at 0..P-1, then each macro-step's fused input at its position),
  * this is the full-sequence forward that the incremental macro-steps must
  * reproduce slot for slot.  Later ham_macro_step calls continue from position
- * d_positions[b][n_inputs-1].  HAM_EINVAL on null pointers, HAM_ECAP if
+ * d_positions[b][n_inputs-1].  Inputs are expected to be finite: rows are
+ * causal tile by tile, so a NaN or infinity at one input reaches, besides every
+ * later input of its sequence, up to 31 inputs before it.  HAM_EINVAL on null pointers, HAM_ECAP if
  * n_inputs > max_prompt + max_steps; later macro-steps return HAM_ECAP once
  * the KV slot capacity is spent. */
 int ham_prefill_embeds(ham_model* m, int32_t batch, const float* d_embeds, const int32_t* d_positions,

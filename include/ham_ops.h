@@ -8,7 +8,8 @@
  *    base layer of ham_macro_step launches, with the same split choice for the
  *    same batch and slot bound;
  *  - ham_op_decode_attention runs the attention over an already filled cache
- *    that the micro decoder's first step uses (a different kernel).
+ *    that a prompt batch's last base layer and the micro decoder's first step
+ *    use (a different kernel).
  * Same conventions as include/ham.h: C functions, HAM_OK or a negative
  * HAM_E* code, ham_last_error() for the message, "d_" = device pointers, work
  * enqueued on `hip_stream` and valid after it is synchronised.
@@ -41,7 +42,8 @@ size_t ham_op_attention_workspace_bytes(int32_t rows, int32_t n_heads, int32_t n
  *               tiles, d-major inside a tile: element (d, slot) at
  *               ((slot/32)*head_dim + d)*32 + slot%32 of its (row, kv head))
  *  d_kv_len     int32 [rows], each <= slots_cap; d_enable int32 [rows]
- *  kv_max       host upper bound of kv_len (chooses the slot split)
+ *  kv_max       host upper bound of kv_len (with rows, n_kv_heads, head_dim and
+ *               dtype it chooses the slot split; rows may be of any lengths)
  *  d_out        act rows [rows][n_heads*head_dim]
  * head_dim 64 or 128, n_heads/n_kv_heads in 1..4, slots_cap a multiple of 64.
  * HAM_EINVAL on a bad shape, HAM_ENOMEM if the workspace is too small. */

@@ -12,10 +12,13 @@
 //
 // k_attn_decode: one workgroup per (query row, kv head, slot split), its waves
 //   sharing the slot range.  The rows of the matrix products are the q-heads
-//   sharing the kv head (GQA).  Waves merge in LDS; splits (long contexts only)
+//   sharing the kv head (GQA).  Waves merge in LDS; splits (attn_decode_splits)
 //   write (max, sum, unnormalised output) and k_attn_combine merges them with
-//   the log-sum-exp rule in split order.  Used for base decode (ragged kv_len per sequence) and the micro
-//   decoder's local cache.
+//   the log-sum-exp rule in split order.  Used for attention over a cache that is
+//   filled already: the attention op, the last base layer of a prompt batch (one
+//   row per sequence) and the micro decoder's first step.
+// k_attn_step: the decode step of the base layers and the later micro steps, which
+//   appends the newest slot itself.
 // k_attn_prefill: the q-heads of a kv head over 16-row groups of a prompt chunk,
 //   key blocks shared through LDS, causal (fp32 models; bf16 prompts run
 //   kernels_attn_prompt.hip).
@@ -265,8 +268,8 @@ __device__ __forceinline__ void attn_merge_store(const AttnLds<HD>& sh, bool ext
 }
 
 // One workgroup per (query row, kv head, slot split) over a cache that already
-// holds every visible slot (the attention op, the micro decoder's first step);
-// its waves take consecutive key blocks of the split's slot range.
+// holds every visible slot (the attention op, a prompt batch's last base layer,
+// the micro decoder's first step); its waves take consecutive key blocks of the split's slot range.
 template <typename T, int HD>
 __global__ __launch_bounds__(64 * ATTN_NW) void k_attn_decode(AttnArgs a) {
   if (!any_flag(a.gate, a.gate_n)) return;

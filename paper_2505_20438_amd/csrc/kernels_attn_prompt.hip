@@ -18,7 +18,8 @@
 // What bounds it: the matrix cores (4 x 2 products per slot, hi and lo halves of q and p) and, nearly as much, the
 // vector instructions of the softmax.  Those are kept to about 11 per score: scale and maximum enter one fused
 // multiply-add before exp2; the running maximum only moves (and rescales the output rows) when some score exceeds it
-// by more than 8 powers of two, so most blocks need no exchange between lanes; sums stay in the lane until the end;
+// by more than 8 powers of two (the conditional rescaling published with FlashAttention-4), so most blocks need no
+// exchange between lanes; sums stay in the lane until the end;
 // masks and the zeroing of values past the end run only in blocks that reach past the wave's first row.  8B shape,
 // 2,048 rows at slots 30,720..32,767: 2,270 -> 1,798 us, 1,185 TFLOP/s executed (16x16x32 products, about 25 vector
 // instructions per score and two exchanges per block before); rows 0..2,047: 155 -> 99 us.
