@@ -12,8 +12,9 @@
 // 2.25 GHz.  Three things bring it to 1,310 cycles at 1.8 GHz (1,240 and 1.75 GHz with no loads in the loop at all):
 // the two groups one phase apart; the loads of a later stage issued by the waves that multiply, one per four matrix
 // instructions (issued together at the head of a phase they hold back its LDS reads and its products for the ~500
-// cycles that the address path takes for them: 1,850 again); 32x32x16 products.  8B shape, 2,048 rows: gate/up
-// 1,016 -> 834 us, down 488 -> 375, o-projection 152 -> 127, q/k/v 253 -> 189.
+// cycles that the address path takes for them: 1,850 again); 32x32x16 products.  8B shape, 2,048 rows, in the prefill of
+// 4 x 32K tokens against the four-wave tile (kernel trace): gate/up 1,027 -> 799 us, down 573 -> 392, o-projection
+// 173 -> 121, q/k/v 222 -> 215; by counters the matrix cores are busy 0.63 of the cycles there, at 1.86 GHz.
 #include <algorithm>
 
 #include "device_common.h"
