@@ -3,9 +3,9 @@ against the oracle at the 8B attention shape (32 q-heads, 8 kv-heads, head dim
 128) with a narrow model (d 512, ffn 1024, vocab 4096, 2 base + 2 micro layers)
 so the float64 oracle can run a multi-thousand-token prefill in seconds.
 
-* batch 8, prompt 5200: the prefill runs three chunks (2048 + 2048 + 1104
-  rows; the later chunks attend over the earlier chunks' cache entries), and
-  every macro-step's fused attention step runs 4 slot splits of about 41 key
+* batch 8, prompt 5200: the prefill runs the batch's 41,600 rows in chunks of up to
+  2,048, which cut the prompts (a prompt's later chunks attend over the cache
+  entries of its earlier ones), and every macro-step's fused attention step runs 4 slot splits of about 41 key
   blocks, so each wave loops over two more key chunks after its first (the
   long-context workload's launch, where each wave takes about 16 blocks);
 * batch 32, prompt 1300: one attention workgroup per (sequence, kv head), each
