@@ -16,8 +16,8 @@ constexpr int MAX_ATTN_SPLIT = 64;
 // 287 / 257; the same where 256 workgroups come out even (1 x 2,048 10.4, 8 x 4,096 29, 32 x 4,096 87, 4 x 32K 89).
 // A row's slots are shared by its own splits alone, so a long row among short ones is a serial chain.  From 2 MB of keys
 // (8,192 such slots: 111 us unsplit) a row gets at least two rounds' share, up to 8 splits.  One row of 32K slots and the
-// rest of 500: 8 rows 126 -> 75 us, 20 rows 444 -> 75, 40 rows 445 -> 129; where all are long this costs 8 x 32K 169 ->
-// 177, 16 x 8,192 89 -> 97 and 32 x 8,192 165 -> 174.
+// rest of 500: 8 rows 126 -> 75 us, 20 rows 444 -> 75, 40 rows 445 -> 129; where all are long this costs up to a tenth (10 x
+// 8,192 61 -> 67 us, 5 x 8,192 35 -> 37, 16 x 8,192 89 -> 97, 32 x 8,192 165 -> 174, 8 x 32K 169 -> 177).
 inline int attn_decode_splits(int dtype, int R, int Hk, int hd, int kv_max) {
   const int es = dtype == 1 ? 2 : 4, kb = dtype == 1 ? 32 : 16;
   const long long keys = (long long)kv_max * hd * es, pairs = (long long)R * Hk;
